@@ -91,7 +91,7 @@ template <class T> __device__ __forceinline__ T ldz(const T* p, int64_t e, bool 
 template <class T, int NDIM>
 __global__ __launch_bounds__(256) void k_adj_pred(const GridDesc* __restrict__ grids, const int2* __restrict__ items,
                                                   int nitems, DevState<T> U, AdjArrays<T> A, double dt0, Phys ph) {
-  const T gam = T(ph.gamma), gm1 = gam - T(1);
+  const T gm1 = T(ph.gamma) - T(1), gm1_inv = drcp(gm1);
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const int2 item = items[it];
     const GridDesc G = grids[item.x];
@@ -121,7 +121,11 @@ __global__ __launch_bounds__(256) void k_adj_pred(const GridDesc* __restrict__ g
     fb[2][0] = NDIM == 3 ? U.f[7][p.e] : T(0);
     fb[2][1] = NDIM == 3 ? U.f[7][p.e + st[2]] : T(0);
     Pred<T, NDIM> pr;
-    (void)predict<T, NDIM>(w, wxm, wxp, wym, wyp, wzm, wzp, fb, ls.hdt, ls.idx, gam, pr);
+    T dzm[8], dzp[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) { dzm[q] = w[q] - wzm[q]; dzp[q] = wzp[q] - w[q]; }
+    const T hcdt[3] = {ls.hdt * ls.idx[0], ls.hdt * ls.idx[1], ls.hdt * ls.idx[2]};
+    (void)predict<T, NDIM>(w, wxm, wxp, wym, wyp, dzm, dzp, fb, hcdt, gm1, gm1_inv, pr);
 #pragma unroll
     for (int d = 0; d < NDIM; ++d)
 #pragma unroll

@@ -38,6 +38,7 @@ __global__ __launch_bounds__(256) void k_flux(const GridDesc* __restrict__ grids
   const int tid = threadIdx.x;
   const T gam = T(ph.gamma);
   const T gm1 = gam - T(1);
+  const T gm1_inv = drcp(gm1);
 
   ItemRange rng = first_claim<PERSIST>(nitems, claim, xcd);
   for (;;) {
@@ -61,15 +62,11 @@ __global__ __launch_bounds__(256) void k_flux(const GridDesc* __restrict__ grids
     const bool act = live && cx >= cl && cx < chx && cy >= cl && cy < chy;
     const bool own = act && tx >= 1 && ty >= 1;
 
-    // time step of this grid's level and 1/dx
+    // half the time step of this grid's level over dx
     double rl = 1.0;
     for (int l = 0; l < G.level; ++l) rl *= (double)ph.ratio;
-    const T dt = T(dt0p[0] / rl);
-    const T hdt = T(0.5) * dt;
-    T idx[3];
-    idx[0] = T(rl / ph.dx0[0]);
-    idx[1] = T(rl / ph.dx0[1]);
-    idx[2] = T(NDIM == 3 ? rl / ph.dx0[2] : 0.0);
+    const T hdt = T(0.5) * T(dt0p[0] / rl);
+    const T hcdt[3] = {hdt * T(rl / ph.dx0[0]), hdt * T(rl / ph.dx0[1]), hdt * T(NDIM == 3 ? rl / ph.dx0[2] : 0.0)};
 
     // own LDS entry and (for the first nring threads) one ring entry
     const int eo = (ty + 1) * kW + tx + 1;
@@ -83,17 +80,20 @@ __global__ __launch_bounds__(256) void k_flux(const GridDesc* __restrict__ grids
     const int kstart = NDIM == 3 ? max(item.z0 - 1, cl) : 0;
     const int kend = NDIM == 3 ? item.z1 : 1;
 
-    T wprev[8], wcur[8], wnext[8], wring[8];
+    T dzm[8], wcur[8], wnext[8], wring[8];  // dzm: wcur minus the plane below
     T fbcur[3][2], fbnext[3][2];  // face fields of the current / next plane's cell
     T zcarry[7];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) { wprev[q] = T(1); wcur[q] = T(1); wnext[q] = T(1); wring[q] = T(1); }
+    for (int q = 0; q < 8; ++q) { dzm[q] = T(0); wcur[q] = T(1); wnext[q] = T(1); wring[q] = T(1); }
 #pragma unroll
     for (int q = 0; q < 7; ++q) zcarry[q] = T(0);
 
     // prologue: W(kstart-1) and W(kstart+1) own (3D), W(kstart) own + ring
     // into LDS; in 3-D the own cell's loads then run two planes ahead (the
     // predictor of plane k needs W(k+1))
+    T wprev[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) wprev[q] = T(1);
     if (NDIM == 3 && ook) load_prim_b<T, NDIM>(U, bx(cx, cy, kstart - 1), bx.sy, bx.sz, gm1, wprev);
 #pragma unroll
     for (int d = 0; d < 3; ++d) fbcur[d][0] = fbcur[d][1] = fbnext[d][0] = fbnext[d][1] = T(0);
@@ -104,6 +104,7 @@ __global__ __launch_bounds__(256) void k_flux(const GridDesc* __restrict__ grids
     for (int q = 0; q < 8; ++q) {
       if (live) sW[q][eo] = wcur[q];
       if (tid < nring) sW[q][rey * kW + rex] = wring[q];
+      dzm[q] = wcur[q] - wprev[q];
     }
     __syncthreads();
 
@@ -119,6 +120,9 @@ __global__ __launch_bounds__(256) void k_flux(const GridDesc* __restrict__ grids
         if (rok) load_raw3<T>(U, bx(rcx, rcy, k + 1), bx.sy, bx.sz, rring, rrfb);
       }
       Pred<T, NDIM> pr;
+      T dzp[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) dzp[q] = wnext[q] - wcur[q];
       if (act) {
         T wxm[8], wxp[8], wym[8], wyp[8];
 #pragma unroll
@@ -132,7 +136,7 @@ __global__ __launch_bounds__(256) void k_flux(const GridDesc* __restrict__ grids
         bool ok;
         if constexpr (UPWIND) {
           T du[8];
-          ok = predict_du<T, NDIM>(wcur, wxm, wxp, wym, wyp, wprev, wnext, fbcur, hdt, idx, gam, pr, du);
+          ok = predict_du<T, NDIM>(wcur, wxm, wxp, wym, wyp, dzm, dzp, fbcur, hcdt, gm1, gm1_inv, pr, du);
           // reference EMF of the upwinded CT: -v x B with v of the half-step
           // cell state U + du and B at time n; one writer per cell (the
           // tile's own cells, plus the grid's first column / row / plane)
@@ -149,7 +153,7 @@ __global__ __launch_bounds__(256) void k_flux(const GridDesc* __restrict__ grids
             stb(F.e[2], eb, vy * wcur[5] - vx * wcur[6]);
           }
         } else {
-          ok = predict<T, NDIM>(wcur, wxm, wxp, wym, wyp, wprev, wnext, fbcur, hdt, idx, gam, pr);
+          ok = predict<T, NDIM>(wcur, wxm, wxp, wym, wyp, dzm, dzp, fbcur, hcdt, gm1, gm1_inv, pr);
         }
         if (!ok) flag_bad(err, ix(cx, cy, k));
 #pragma unroll
@@ -170,7 +174,7 @@ __global__ __launch_bounds__(256) void k_flux(const GridDesc* __restrict__ grids
         for (int q = 0; q < 8; ++q) {
           if (live) sW[q][eo] = wnext[q];
           if (tid < nring) sW[q][rey * kW + rex] = wring[q];
-          wprev[q] = wcur[q];
+          dzm[q] = dzp[q];
           wcur[q] = wnext[q];
         }
 #pragma unroll
@@ -194,7 +198,7 @@ __global__ __launch_bounds__(256) void k_flux(const GridDesc* __restrict__ grids
           T l[7];
 #pragma unroll
           for (int q = 0; q < 7; ++q) l[q] = sX[q][tid - 1];
-          hlld7(l, pr.m[0], bn[0], gam, f);
+          hlld7(l, pr.m[0], bn[0], gam, gm1_inv, f);
 #pragma unroll
           for (int q = 0; q < 7; ++q) stb(F.f[0][q], eb, f[q]);
         }
@@ -202,12 +206,12 @@ __global__ __launch_bounds__(256) void k_flux(const GridDesc* __restrict__ grids
           T l[7];
 #pragma unroll
           for (int q = 0; q < 7; ++q) l[q] = sY[q][tid - tw];
-          hlld7(l, pr.m[1], bn[1], gam, f);
+          hlld7(l, pr.m[1], bn[1], gam, gm1_inv, f);
 #pragma unroll
           for (int q = 0; q < 7; ++q) stb(F.f[1][q], eb, f[q]);
         }
         if (NDIM == 3 && k > cl) {
-          hlld7(zcarry, pr.m[2], bn[2], gam, f);
+          hlld7(zcarry, pr.m[2], bn[2], gam, gm1_inv, f);
 #pragma unroll
           for (int q = 0; q < 7; ++q) stb(F.f[2][q], eb, f[q]);
         }

@@ -181,26 +181,26 @@ struct Pred {
 };
 
 // Slopes, face states, Hancock increment and predicted states of one cell.
-// wx/wy/wz hold the neighbours (minus, plus) along each axis; fb[d][0/1] are
-// the cell's low/high face fields along d.  Each predicted state is handed to
-// emit(d, side, q) as soon as it is formed (side 0 low, 1 high), so callers
-// that store it right away never hold all 2*NDIM states in registers.
-// Returns false if a predicted density or pressure is not positive.
-// When WANT_DU, du_out receives the Hancock increment of the cell's
-// conserved state.
+// wx/wy hold the neighbours (minus, plus) along x and y, dzm and dzp the
+// differences to the cell below and above (a kernel marching along z has
+// formed dzm as the last plane's dzp); fb[d][0/1] are the cell's low/high
+// face fields along d, hcdt[d] half dt / dx_d.  Each pair of predicted states
+// of a direction is handed to emit(d, low, high) as soon as it is formed, so
+// callers that store it right away never hold all 2*NDIM states in
+// registers.  Returns false if a predicted density or pressure is not
+// positive.  When WANT_DU, du_out receives the Hancock increment of the
+// cell's conserved state.
 template <class T, int NDIM, bool WANT_DU = false, class Emit>
 __device__ __forceinline__ bool predict_emit(const T (&w)[8], const T (&wxm)[8], const T (&wxp)[8],
-                                             const T (&wym)[8], const T (&wyp)[8], const T (&wzm)[8],
-                                             const T (&wzp)[8], const T (&fb)[3][2], T hdt, const T (&idx)[3], T gam,
-                                             Emit&& emit, T (&du_out)[8]) {
-  const T gm1 = gam - T(1);
-  const T gm1_inv = drcp(gm1);
+                                             const T (&wym)[8], const T (&wyp)[8], const T (&dzm)[8],
+                                             const T (&dzp)[8], const T (&fb)[3][2], const T (&hcdt)[3], T gm1,
+                                             T gm1_inv, Emit&& emit, T (&du_out)[8]) {
   T sl[3][8];
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
     sl[0][q] = limiter_minmod(w[q] - wxm[q], wxp[q] - w[q]);
     sl[1][q] = limiter_minmod(w[q] - wym[q], wyp[q] - w[q]);
-    if (NDIM == 3) sl[2][q] = limiter_minmod(w[q] - wzm[q], wzp[q] - w[q]);
+    if (NDIM == 3) sl[2][q] = limiter_minmod(dzm[q], dzp[q]);
   }
   T du[8];
 #pragma unroll
@@ -225,9 +225,8 @@ __device__ __forceinline__ bool predict_emit(const T (&w)[8], const T (&wxm)[8],
       flux_along<2>(wl, fl, gm1_inv);
       flux_along<2>(wr, fr, gm1_inv);
     }
-    const T c = hdt * idx[d];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) du[q] -= c * (fr[q] - fl[q]);
+    for (int q = 0; q < 8; ++q) du[q] -= hcdt[d] * (fr[q] - fl[q]);
   }
   if constexpr (WANT_DU) {
 #pragma unroll
@@ -236,59 +235,70 @@ __device__ __forceinline__ bool predict_emit(const T (&w)[8], const T (&wxm)[8],
   bool ok = true;
 #pragma unroll
   for (int d = 0; d < NDIM; ++d) {
+    T us[2][8], ir[2], q7[2][7];
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
-      T ws[8], us[8], wb[8];
+      T ws[8];
       const T h = side ? T(0.5) : T(-0.5);
 #pragma unroll
       for (int q = 0; q < 8; ++q) ws[q] = w[q] + h * sl[d][q];
       ws[5 + d] = fb[d][side];
-      to_conserved(ws, us, gm1_inv);
+      to_conserved(ws, us[side], gm1_inv);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) us[q] += du[q];
-      to_primitive(us, wb, gm1);
-      ok = ok && (wb[0] > T(0)) && (wb[4] > T(0));
-      T q7[7];
-      if (d == 0) rotate7<0>(wb, q7);
-      else if (d == 1) rotate7<1>(wb, q7);
-      else rotate7<2>(wb, q7);
-      emit(d, side, q7);
+      for (int q = 0; q < 8; ++q) us[side][q] += du[q];
     }
+    drcp2(us[0][0], us[1][0], ir[0], ir[1]);
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      T wb[8];
+      to_primitive_ir(us[side], wb, gm1, ir[side]);
+      ok = ok && (wb[0] > T(0)) && (wb[4] > T(0));
+      if (d == 0) rotate7<0>(wb, q7[side]);
+      else if (d == 1) rotate7<1>(wb, q7[side]);
+      else rotate7<2>(wb, q7[side]);
+    }
+    emit(d, q7[0], q7[1]);
   }
   return ok;
 }
 
 template <class T, int NDIM>
 __device__ __forceinline__ bool predict(const T (&w)[8], const T (&wxm)[8], const T (&wxp)[8], const T (&wym)[8],
-                                        const T (&wyp)[8], const T (&wzm)[8], const T (&wzp)[8],
-                                        const T (&fb)[3][2], T hdt, const T (&idx)[3], T gam,
+                                        const T (&wyp)[8], const T (&dzm)[8], const T (&dzp)[8],
+                                        const T (&fb)[3][2], const T (&hcdt)[3], T gm1, T gm1_inv,
                                         Pred<T, NDIM>& out) {
   T unused[8];
-  return predict_emit<T, NDIM>(w, wxm, wxp, wym, wyp, wzm, wzp, fb, hdt, idx, gam,
-                               [&](int d, int side, const T (&q)[7]) {
+  return predict_emit<T, NDIM>(w, wxm, wxp, wym, wyp, dzm, dzp, fb, hcdt, gm1, gm1_inv,
+                               [&](int d, const T (&lo)[7], const T (&hi)[7]) {
 #pragma unroll
-                                 for (int c = 0; c < 7; ++c) (side ? out.p[d] : out.m[d])[c] = q[c];
+                                 for (int c = 0; c < 7; ++c) {
+                                   out.m[d][c] = lo[c];
+                                   out.p[d][c] = hi[c];
+                                 }
                                }, unused);
 }
 
 // predict() that also returns the Hancock increment du of the cell.
 template <class T, int NDIM>
 __device__ __forceinline__ bool predict_du(const T (&w)[8], const T (&wxm)[8], const T (&wxp)[8], const T (&wym)[8],
-                                           const T (&wyp)[8], const T (&wzm)[8], const T (&wzp)[8],
-                                           const T (&fb)[3][2], T hdt, const T (&idx)[3], T gam,
+                                           const T (&wyp)[8], const T (&dzm)[8], const T (&dzp)[8],
+                                           const T (&fb)[3][2], const T (&hcdt)[3], T gm1, T gm1_inv,
                                            Pred<T, NDIM>& out, T (&du)[8]) {
-  return predict_emit<T, NDIM, true>(w, wxm, wxp, wym, wyp, wzm, wzp, fb, hdt, idx, gam,
-                                     [&](int d, int side, const T (&q)[7]) {
+  return predict_emit<T, NDIM, true>(w, wxm, wxp, wym, wyp, dzm, dzp, fb, hcdt, gm1, gm1_inv,
+                                     [&](int d, const T (&lo)[7], const T (&hi)[7]) {
 #pragma unroll
-                                       for (int c = 0; c < 7; ++c) (side ? out.p[d] : out.m[d])[c] = q[c];
+                                       for (int c = 0; c < 7; ++c) {
+                                         out.m[d][c] = lo[c];
+                                         out.p[d][c] = hi[c];
+                                       }
                                      }, du);
 }
 
 template <class T>
-__device__ __forceinline__ void hlld7(const T (&l)[7], const T (&r)[7], T bn, T gam, T (&f)[7]) {
+__device__ __forceinline__ void hlld7(const T (&l)[7], const T (&r)[7], T bn, T gam, T gm1_inv, T (&f)[7]) {
   T ql[8] = {l[0], l[1], l[2], l[3], l[4], bn, l[5], l[6]};
   T qr[8] = {r[0], r[1], r[2], r[3], r[4], bn, r[5], r[6]};
-  riemann_hlld(ql, qr, bn, gam, f);
+  riemann_hlld(ql, qr, bn, gam, gm1_inv, f);
 }
 
 

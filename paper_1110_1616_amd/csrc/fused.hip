@@ -73,7 +73,7 @@ __global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grid
                                                DevFlux<T> F, const uint8_t* __restrict__ fmask,
                                                const double* __restrict__ dt0p, Phys ph, ErrBlock* err, WorkQueue* q,
                                                bool xcd, int claim) {
-  __shared__ T sW[8][kMaxPlane];
+  __shared__ T sW[8][kMaxPlane + 1];  // (the last entry takes the writes of lanes outside the tile)
   __shared__ T sX[7][256];
   __shared__ T sY[7][256];
   __shared__ T sH[2][10][256];  // hydro components 0..4 of the x- (0..4) and y-face (5..9) fluxes, by plane parity
@@ -87,6 +87,7 @@ __global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grid
   const int tid = threadIdx.x;
   const T gam = T(ph.gamma);
   const T gm1 = gam - T(1);
+  const T gm1_inv = drcp(gm1);
 
   ItemRange rng = first_claim<PERSIST>(nitems, claim, xcd);
   for (;;) {
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grid
     const bool live = ty < th;
     const int cx = x0 - 1 + tx, cy = y0 - 1 + ty;
     const bool act = live && cx >= cl && cx < chx && cy >= cl && cy < chy;
-    const bool xf = act && tx >= 1 && cx > cl;  // solves its cell's low x-face
+    const bool xf = act && tx >= 1 && cx > cl;  // its cell's low x-face is a face of the launch
     const bool yf = act && ty >= 1 && cy > cl;  // low y-face
     // update ownership: cells and z-faces at interior lanes; x- and y-faces
     // also the update region's last face (uh), wherever it falls
@@ -120,26 +121,33 @@ __global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grid
     const bool ucell = live && ucol && urow;
     const bool ubx = live && urow && (ucol || (tx >= 1 && cx == uhx));
     const bool uby = live && ucol && (urow || (ty >= 1 && cy == uhy));
-    // flux stores for the registers: one owning lane per computed face
-    const bool sxy_x = owns(tx, tw, cx, cl, chx - 1), sxy_y = owns(ty, th, cy, cl, chy - 1);
+    // flux stores for the registers: one owning lane per computed face (mask
+    // bits of the faces this lane stores)
+    const bool sxy = owns(tx, tw, cx, cl, chx - 1) && owns(ty, th, cy, cl, chy - 1);
+    const unsigned smask = sxy ? (xf ? 1u : 0u) | (yf ? 2u : 0u) | (act ? 4u : 0u) : 0u;
+    // Every lane runs the whole plane: lanes without a cell of the launch
+    // load a clamped cell of the box and read clamped LDS entries, and what
+    // they form is used by nobody (a lone wave of a SIMD issues one
+    // instruction every four cycles, scalar or vector, so execution masks
+    // around each piece cost more than the idle lanes).
+    const int lx = min(max(cx, wlo), whix - 1), ly = min(max(cy, wlo), whiy - 1);
+    const int tl = max(tid - 1, 0), td = max(tid - tw, 0);        // low x and y neighbours
+    const int tr = min(tid + 1, 255), tu = min(tid + tw, 255);    // high ones
 
     double rl = 1.0;
     for (int l = 0; l < G.level; ++l) rl *= (double)ph.ratio;
     const T dt = T(dt0p[0] / rl);
-    const T hdt = T(0.5) * dt;
-    T idx[3];
-    idx[0] = T(rl / ph.dx0[0]);
-    idx[1] = T(rl / ph.dx0[1]);
-    idx[2] = T(NDIM == 3 ? rl / ph.dx0[2] : 0.0);
-    const T cdx = dt * idx[0], cdy = dt * idx[1], cdz = dt * idx[2];
+    const T cdx = dt * T(rl / ph.dx0[0]), cdy = dt * T(rl / ph.dx0[1]);
+    const T cdz = dt * T(NDIM == 3 ? rl / ph.dx0[2] : 0.0);
 
-    const int eo = (ty + 1) * kW + tx + 1;
+    const int eo = live ? (ty + 1) * kW + tx + 1 : kW + 1;  // LDS plane entry read around
+    const int ew = live ? eo : kMaxPlane;                   // and written
     const int nring = 2 * (tw + th);
     int rex = 0, rey = 0;
     if (tid < nring) ring_entry(tid, tw, th, rex, rey);
     const int rcx = x0 - 2 + rex, rcy = y0 - 2 + rey;
-    const bool rok = tid < nring && rcx >= wlo && rcx < whix && rcy >= wlo && rcy < whiy;
-    const bool ook = live && cx >= wlo && cx < whix && cy >= wlo && cy < whiy;
+    const bool ring = tid < nring;
+    const bool rok = ring && rcx >= wlo && rcx < whix && rcy >= wlo && rcy < whiy;
 
     // planes: update planes [z0, z1) (cells below uhz; z-faces up to uhz);
     // predicted states from z0 - 1 to the last plane whose fluxes they need
@@ -147,13 +155,13 @@ __global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grid
     const int kstart = NDIM == 3 ? z0 - 1 : 0;
     const int kend = NDIM == 3 ? min(z1, uhz) : 0;  // inclusive
 
-    T wprev[8], wcur[8], wnext[8], wring[8];
+    T dzm[8], wcur[8], wnext[8], wring[8];  // dzm: wcur minus the plane below
     T fbcur[3][2], fbnext[3][2];
     T zcarry[7];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) { wprev[c] = T(1); wcur[c] = T(1); wnext[c] = T(1); wring[c] = T(1); }
+    for (int c = 0; c < 8; ++c) { dzm[c] = T(0); wnext[c] = T(1); wring[c] = T(1); }
 #pragma unroll
-    for (int c = 0; c < 7; ++c) zcarry[c] = T(0);
+    for (int c = 0; c < 7; ++c) zcarry[c] = T(1);
     // carried from the previous plane: z-flux hydro components at k - 1/2,
     // E_x and E_y at the low z-edges, F_y c5 and F_x c6 of the plane
     T fzp[5] = {T(0), T(0), T(0), T(0), T(0)};
@@ -163,45 +171,47 @@ __global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grid
     for (int d = 0; d < 3; ++d) fbcur[d][0] = fbcur[d][1] = fbnext[d][0] = fbnext[d][1] = T(0);
     if (NDIM == 3) {
       // the item's first planes: every load issued before any conversion
-      T r0[5], r1[5], r2[5], rr[5], f0[3][2], fr[3][2];
-      if (ook) {
-        load_raw3<T>(U, bx(cx, cy, kstart - 1), bx.sy, bx.sz, r0, f0);
-        load_raw3<T>(U, bx(cx, cy, kstart), bx.sy, bx.sz, r1, fbcur);
-        load_raw3<T>(U, bx(cx, cy, kstart + 1), bx.sy, bx.sz, r2, fbnext);
-      }
+      T r0[5], r1[5], r2[5], rr[5], f0[3][2], fr[3][2], wprev[8];
+      load_raw3<T>(U, bx(lx, ly, kstart - 1), bx.sy, bx.sz, r0, f0);
+      load_raw3<T>(U, bx(lx, ly, kstart), bx.sy, bx.sz, r1, fbcur);
+      load_raw3<T>(U, bx(lx, ly, kstart + 1), bx.sy, bx.sz, r2, fbnext);
       if (rok) load_raw3<T>(U, bx(rcx, rcy, kstart), bx.sy, bx.sz, rr, fr);
-      if (ook) {
-        raw3_to_prim<T>(r0, f0, gm1, wprev);
-        raw3_to_prim<T>(r1, fbcur, gm1, wcur);
-        raw3_to_prim<T>(r2, fbnext, gm1, wnext);
-      }
+      raw3_to_prim<T>(r0, f0, gm1, wprev);
+      raw3_to_prim<T>(r1, fbcur, gm1, wcur);
+      raw3_to_prim<T>(r2, fbnext, gm1, wnext);
       if (rok) raw3_to_prim<T>(rr, fr, gm1, wring);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) dzm[c] = wcur[c] - wprev[c];
     } else {
-      if (ook) load_prim_faces_b<T, NDIM>(U, bx(cx, cy, kstart), bx.sy, bx.sz, gm1, wcur, fbcur);
+      load_prim_faces_b<T, NDIM>(U, bx(lx, ly, kstart), bx.sy, bx.sz, gm1, wcur, fbcur);
       if (rok) load_prim_b<T, NDIM>(U, bx(rcx, rcy, kstart), bx.sy, bx.sz, gm1, wring);
     }
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-      if (live) sW[c][eo] = wcur[c];
-      if (tid < nring) sW[c][rey * kW + rex] = wring[c];
+      sW[c][ew] = wcur[c];
+      if (ring) sW[c][rey * kW + rex] = wring[c];
     }
     __syncthreads();
 
-    uint8_t mknext = (fmask && act) ? fmask[ix(cx, cy, kstart)] : uint8_t(0);
+    unsigned mknext = fmask ? fmask[ix(lx, ly, kstart)] : 0u;
     for (int k = kstart; k <= kend; ++k) {
       const int pb = k & 1;
       // this plane's face mask was loaded an iteration ago; the next one's
       // load is in flight through this iteration
-      const uint8_t mk = mknext;
-      if (fmask && act && k + 1 <= kend) mknext = fmask[ix(cx, cy, k + 1)];
+      const unsigned mk = mknext & smask;
+      if (fmask && k + 1 <= kend) mknext = fmask[ix(lx, ly, k + 1)];
       T rnext[5], rfb[3][2], rring[5], rrfb[3][2];
-      const bool pf = NDIM == 3 && ook && k + 2 <= kend + 1;
+      const bool rn = NDIM == 3 && rok && k + 1 <= kend;
       if (NDIM == 3) {
-        if (pf) load_raw3<T>(U, bx(cx, cy, k + 2), bx.sy, bx.sz, rnext, rfb);
-        if (rok && k + 1 <= kend) load_raw3<T>(U, bx(rcx, rcy, k + 1), bx.sy, bx.sz, rring, rrfb);
+        // (the last iterations load the last plane again: no branch)
+        load_raw3<T>(U, bx(lx, ly, min(k + 2, kend + 1)), bx.sy, bx.sz, rnext, rfb);
+        if (rn) load_raw3<T>(U, bx(rcx, rcy, k + 1), bx.sy, bx.sz, rring, rrfb);
       }
       Pred<T, NDIM> pr;
-      if (act) {
+      T dzp[8];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) dzp[c] = wnext[c] - wcur[c];
+      {
         T wxm[8], wxp[8], wym[8], wyp[8];
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
@@ -210,9 +220,9 @@ __global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grid
           wym[c] = sW[c][eo - kW];
           wyp[c] = sW[c][eo + kW];
         }
-        if ((wcur[0] <= T(0)) || (wcur[4] <= T(0))) flag_bad(err, ix(cx, cy, k));
-        const bool ok = predict<T, NDIM>(wcur, wxm, wxp, wym, wyp, wprev, wnext, fbcur, hdt, idx, gam, pr);
-        if (!ok) flag_bad(err, ix(cx, cy, k));
+        const T hcdt[3] = {T(0.5) * cdx, T(0.5) * cdy, T(0.5) * cdz};
+        const bool ok = predict<T, NDIM>(wcur, wxm, wxp, wym, wyp, dzm, dzp, fbcur, hcdt, gm1, gm1_inv, pr);
+        if (act && (!ok || wcur[0] <= T(0) || wcur[4] <= T(0))) flag_bad(err, ix(cx, cy, k));
 #pragma unroll
         for (int c = 0; c < 7; ++c) {
           sX[c][tid] = pr.p[0][c];
@@ -224,12 +234,12 @@ __global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grid
       // the Riemann problems run
       T bn[3] = {fbcur[0][0], fbcur[1][0], fbcur[2][0]};
       if (NDIM == 3) {
-        if (rok && k + 1 <= kend) raw3_to_prim<T>(rring, rrfb, gm1, wring);
+        if (rn) raw3_to_prim<T>(rring, rrfb, gm1, wring);
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-          if (live) sW[c][eo] = wnext[c];
-          if (tid < nring) sW[c][rey * kW + rex] = wring[c];
-          wprev[c] = wcur[c];
+          sW[c][ew] = wnext[c];
+          if (ring) sW[c][rey * kW + rex] = wring[c];
+          dzm[c] = dzp[c];
           wcur[c] = wnext[c];
         }
 #pragma unroll
@@ -237,40 +247,36 @@ __global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grid
           fbcur[d][0] = fbnext[d][0];
           fbcur[d][1] = fbnext[d][1];
         }
-        if (pf) {
-          raw3_to_prim<T>(rnext, rfb, gm1, wnext);
+        raw3_to_prim<T>(rnext, rfb, gm1, wnext);
 #pragma unroll
-          for (int d = 0; d < 3; ++d) {
-            fbnext[d][0] = rfb[d][0];
-            fbnext[d][1] = rfb[d][1];
-          }
+        for (int d = 0; d < 3; ++d) {
+          fbnext[d][0] = rfb[d][0];
+          fbnext[d][1] = rfb[d][1];
         }
       }
-      const bool zf = NDIM == 3 && act && k >= z0;
-      const auto eb = bx(cx, cy, k);
+      const bool zf = NDIM == 3 && k >= z0;
+      const auto eb = bx(lx, ly, k);
       T fx[7], fy[7], fz[7];
 #pragma unroll
-      for (int c = 0; c < 7; ++c) { fx[c] = T(0); fy[c] = T(0); fz[c] = T(0); }
-      if (xf) {
+      for (int c = 0; c < 7; ++c) fz[c] = T(0);
+      {
         T l[7];
 #pragma unroll
-        for (int c = 0; c < 7; ++c) l[c] = sX[c][tid - 1];
-        hlld7(l, pr.m[0], bn[0], gam, fx);
-        if ((mk & 1u) && sxy_x && sxy_y && (NDIM == 2 || (k >= z0 && k < z1) || (k == kstart && z0 == ul)))
-          st_flux7(F, 0, eb, fx);
+        for (int c = 0; c < 7; ++c) l[c] = sX[c][tl];
+        hlld7(l, pr.m[0], bn[0], gam, gm1_inv, fx);
       }
-      if (yf) {
+      {
         T l[7];
 #pragma unroll
-        for (int c = 0; c < 7; ++c) l[c] = sY[c][tid - tw];
-        hlld7(l, pr.m[1], bn[1], gam, fy);
-        if ((mk & 2u) && sxy_x && sxy_y && (NDIM == 2 || (k >= z0 && k < z1) || (k == kstart && z0 == ul)))
-          st_flux7(F, 1, eb, fy);
+        for (int c = 0; c < 7; ++c) l[c] = sY[c][td];
+        hlld7(l, pr.m[1], bn[1], gam, gm1_inv, fy);
       }
-      if (zf) {
-        hlld7(zcarry, pr.m[2], bn[2], gam, fz);
-        if ((mk & 4u) && sxy_x && sxy_y && k < z1)
-          st_flux7(F, 2, eb, fz);
+      if (zf) hlld7(zcarry, pr.m[2], bn[2], gam, gm1_inv, fz);
+      if (mk != 0u) {
+        const bool own = NDIM == 2 || (k >= z0 && k < z1);
+        if ((mk & 1u) && (own || (k == kstart && z0 == ul))) st_flux7(F, 0, eb, fx);
+        if ((mk & 2u) && (own || (k == kstart && z0 == ul))) st_flux7(F, 1, eb, fy);
+        if (NDIM == 3 && (mk & 4u) && own) st_flux7(F, 2, eb, fz);
       }
       if (NDIM == 3) {
 #pragma unroll
@@ -295,61 +301,47 @@ __global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grid
       __syncthreads();
       // edge EMFs: E_z at (cx - 1/2, cy - 1/2) of plane k; E_x at
       // (cx, cy - 1/2) and E_y at (cx - 1/2, cy), both at z = k - 1/2
-      if (xf && yf) sEz[pb][tid] = emf_mean(sB[0][tid - tw], fx[5], sB[1][tid - 1], fy[6]);
-      T ex = T(0), ey = T(0);
-      if (NDIM == 3 && k >= z0) {
-        if (yf) ex = emf_mean(fy5p, fy[5], sB[3][tid - tw], fz[6]);
-        if (xf) ey = emf_mean(sB[2][tid - 1], fz[5], fx6p, fx[6]);
-      }
+      sEz[pb][tid] = emf_mean(sB[0][td], fx[5], sB[1][tl], fy[6]);
       // 2-D: the faces read E_z of the neighbours' corners, formed above; in
       // 3-D every input of this plane's update is in LDS already (E_z of the
       // plane below, and the inputs of the neighbours' E_x, E_y)
       if (NDIM == 2) __syncthreads();
       if (NDIM == 3) {
+        const T ex = emf_mean(fy5p, fy[5], sB[3][td], fz[6]);
+        const T ey = emf_mean(sB[2][tl], fz[5], fx6p, fx[6]);
         // the old values of everything this plane updates are loaded before
         // any store, so their latencies overlap
         const int kk = k - 1;
         const bool zup = ucell && k >= z0 && k < z1;
         const bool cup = kk >= z0 && kk < z1 && kk < uhz;
-        const auto ec = bx(cx, cy, kk);
+        const auto ec = bx(lx, ly, kk);
         T uo[8];
+        uo[7] = ldb(U.f[7], eb);
 #pragma unroll
-        for (int s = 0; s < 8; ++s) uo[s] = T(0);
-        if (zup) uo[7] = ldb(U.f[7], eb);
-        if (cup && ucell)
-#pragma unroll
-          for (int s = 0; s < 5; ++s) uo[s] = ldb(U.f[s], ec);
-        if (cup && ubx) uo[5] = ldb(U.f[5], ec);
-        if (cup && uby) uo[6] = ldb(U.f[6], ec);
-        // z-faces at k - 1/2 (element of plane k)
-        if (zup) {
-          // E_y of the next lane's and E_x of the next row's low z-edge,
-          // from the same inputs as those lanes form them
-          const int qb = kk & 1;
-          const T ey1 = emf_mean(sB[2][tid], sB[2][tid + 1], sX6[qb][tid + 1], sX6[pb][tid + 1]);
-          const T ex1 = emf_mean(sY5[qb][tid + tw], sY5[pb][tid + tw], sB[3][tid], sB[3][tid + tw]);
-          stb(V.f[7], eb, uo[7] - curl_delta(cdx, ey1, ey, cdy, ex1, ex));
-        }
+        for (int s = 0; s < 7; ++s) uo[s] = ldb(U.f[s], ec);
+        // z-faces at k - 1/2 (element of plane k): E_y of the next lane's and
+        // E_x of the next row's low z-edge, from the same inputs as those
+        // lanes form them
+        const int qb = kk & 1;
+        const T ey1 = emf_mean(sB[2][tid], sB[2][tr], sX6[qb][tr], sX6[pb][tr]);
+        const T ex1 = emf_mean(sY5[qb][tu], sY5[pb][tu], sB[3][tid], sB[3][tu]);
+        if (zup) stb(V.f[7], eb, uo[7] - curl_delta(cdx, ey1, ey, cdy, ex1, ex));
         // cells and x-, y-faces of plane k - 1
         if (cup) {
-          const int qb = kk & 1;
-          if (ucell) {
+          const T ez0 = sEz[qb][tid], ezy = sEz[qb][tu], ezx = sEz[qb][tr];
+          T un[5];
 #pragma unroll
-            for (int s = 0; s < 5; ++s) {
-              const int qx = hydro_comp(s, 0), qy = hydro_comp(s, 1), qz = hydro_comp(s, 2);
-              const T acc = flux_delta<T, 3>(cdx, sH[qb][qx][tid + 1], sH[qb][qx][tid], cdy, sH[qb][5 + qy][tid + tw],
-                                             sH[qb][5 + qy][tid], cdz, fz[qz], fzp[qz]);
-              stb(V.f[s], ec, uo[s] - acc);
-            }
+          for (int s = 0; s < 5; ++s) {
+            const int qx = hydro_comp(s, 0), qy = hydro_comp(s, 1), qz = hydro_comp(s, 2);
+            const T acc = flux_delta<T, 3>(cdx, sH[qb][qx][tr], sH[qb][qx][tid], cdy, sH[qb][5 + qy][tu],
+                                           sH[qb][5 + qy][tid], cdz, fz[qz], fzp[qz]);
+            un[s] = uo[s] - acc;
           }
-          if (ubx) {
-            const T ez0 = sEz[qb][tid], ez1 = sEz[qb][tid + tw];
-            stb(V.f[5], ec, uo[5] - curl_delta(cdy, ez1, ez0, cdz, ey, eyp_));
-          }
-          if (uby) {
-            const T ez0 = sEz[qb][tid], ez1 = sEz[qb][tid + 1];
-            stb(V.f[6], ec, uo[6] - curl_delta(cdz, ex, exp_, cdx, ez1, ez0));
-          }
+          if (ucell)
+#pragma unroll
+            for (int s = 0; s < 5; ++s) stb(V.f[s], ec, un[s]);
+          if (ubx) stb(V.f[5], ec, uo[5] - curl_delta(cdy, ezy, ez0, cdz, ey, eyp_));
+          if (uby) stb(V.f[6], ec, uo[6] - curl_delta(cdz, ex, exp_, cdx, ezx, ez0));
         }
 #pragma unroll
         for (int c = 0; c < 5; ++c) fzp[c] = fz[c];
@@ -359,26 +351,22 @@ __global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grid
         fx6p = fx[6];
       } else {
         // 2-D: the single plane's cells (B_z cell-centred) and faces
+        T uo[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) uo[s] = ldb(U.f[s], eb);
         if (ucell) {
 #pragma unroll
           for (int s = 0; s < 5; ++s) {
             const int qx = hydro_comp(s, 0), qy = hydro_comp(s, 1);
-            const T acc = flux_delta<T, 2>(cdx, sH[0][qx][tid + 1], sH[0][qx][tid], cdy, sH[0][5 + qy][tid + tw],
+            const T acc = flux_delta<T, 2>(cdx, sH[0][qx][tr], sH[0][qx][tid], cdy, sH[0][5 + qy][tu],
                                            sH[0][5 + qy][tid], T(0), T(0), T(0));
-            stb(V.f[s], eb, ldb(U.f[s], eb) - acc);
+            stb(V.f[s], eb, uo[s] - acc);
           }
-          const T acc = flux_delta<T, 2>(cdx, sB[2][tid + 1], sB[2][tid], cdy, sB[3][tid + tw], sB[3][tid], T(0), T(0),
-                                         T(0));
-          stb(V.f[7], eb, ldb(U.f[7], eb) - acc);
+          const T acc = flux_delta<T, 2>(cdx, sB[2][tr], sB[2][tid], cdy, sB[3][tu], sB[3][tid], T(0), T(0), T(0));
+          stb(V.f[7], eb, uo[7] - acc);
         }
-        if (ubx) {
-          const T e0 = sEz[0][tid], e1 = sEz[0][tid + tw];
-          stb(V.f[5], eb, ldb(U.f[5], eb) - face_delta2(cdy, e1, e0));
-        }
-        if (uby) {
-          const T e0 = sEz[0][tid], e1 = sEz[0][tid + 1];
-          stb(V.f[6], eb, ldb(U.f[6], eb) + face_delta2(cdx, e1, e0));
-        }
+        if (ubx) stb(V.f[5], eb, uo[5] - face_delta2(cdy, sEz[0][tu], sEz[0][tid]));
+        if (uby) stb(V.f[6], eb, uo[6] + face_delta2(cdx, sEz[0][tr], sEz[0][tid]));
       }
     }
     __syncthreads();

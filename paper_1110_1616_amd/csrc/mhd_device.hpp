@@ -79,12 +79,93 @@ __host__ __forceinline__ double psqrt(double x) { return x > 0.0 ? __builtin_sqr
 __host__ __forceinline__ float psqrt(float x) { return x > 0.0f ? __builtin_sqrtf(x) : 0.0f; }
 template <class T> __host__ __device__ __forceinline__ T psqrt(T x) { return x > T(0) ? dsqrt(x) : T(0); }
 
+// Square root s and reciprocal square root i of a positive finite x.  On the
+// device in double: the hardware estimate y (good to about 2^-23) and one
+// third-order step, 1/sqrt(x) = y (1 + e/2 + 3 e^2/8 + ...) with e = 1 - x y^2,
+// whose remainder is below 2^-66: both roots to about 1 ulp for 8 instructions
+// (a correctly rounded root and the reciprocal of it take 18).  In float the
+// hardware root and reciprocal root, 1 ulp each.
+__device__ __forceinline__ void sqrt_rsqrt(double x, double& s, double& i) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double t = x * y;
+  const double e = __builtin_fma(-t, y, 1.0);
+  const double p = __builtin_fma(e, 0.375, 0.5);
+  s = __builtin_fma(t * e, p, t);
+  i = __builtin_fma(y * e, p, y);
+}
+__device__ __forceinline__ void sqrt_rsqrt(float x, float& s, float& i) {
+  s = __builtin_amdgcn_sqrtf(x);
+  i = __builtin_amdgcn_rsqf(x);
+}
+template <class T> __host__ __device__ __forceinline__ void sqrt_rsqrt(T x, T& s, T& i) {
+  s = dsqrt(x);
+  i = drcp(s);
+}
+__host__ __forceinline__ void sqrt_rsqrt(double x, double& s, double& i) { s = __builtin_sqrt(x); i = 1.0 / s; }
+__host__ __forceinline__ void sqrt_rsqrt(float x, float& s, float& i) { s = __builtin_sqrtf(x); i = 1.0f / s; }
+// sqrt(z / r) of positive finite z and r: in double z / sqrt(z r) by the step
+// above (8 instructions; the reciprocal, the product and the correctly
+// rounded root take 19), in float the hardware reciprocal and root.
+__device__ __forceinline__ double sqrt_ratio(double z, double r) {
+  const double w = z * r;
+  const double y = __builtin_amdgcn_rsq(w);
+  const double c = z * y;
+  const double e = __builtin_fma(-(w * y), y, 1.0);
+  const double p = __builtin_fma(e, 0.375, 0.5);
+  return __builtin_fma(c * e, p, c);
+}
+__device__ __forceinline__ float sqrt_ratio(float z, float r) {
+  return __builtin_amdgcn_sqrtf(z * __builtin_amdgcn_rcpf(r));
+}
+template <class T> __host__ __device__ __forceinline__ T sqrt_ratio(T z, T r) { return dsqrt(z * drcp(r)); }
+__host__ __forceinline__ double sqrt_ratio(double z, double r) { return __builtin_sqrt(z / r); }
+__host__ __forceinline__ float sqrt_ratio(float z, float r) { return __builtin_sqrtf(z / r); }
+// Reciprocals of a and b (nonzero, a b finite and normal): in double one
+// refined estimate of the product's, so one transcendental instruction (a
+// quarter of the rate of the others) for the two; in float, whose range
+// bounds the product and whose reciprocal is one instruction, each its own.
+__device__ __forceinline__ void drcp2(double a, double b, double& ia, double& ib) {
+  const double r = drcp(a * b);
+  ia = r * b;
+  ib = r * a;
+}
+__host__ __forceinline__ void drcp2(double a, double b, double& ia, double& ib) { ia = 1.0 / a; ib = 1.0 / b; }
+template <class T> __host__ __device__ __forceinline__ void drcp2(T a, T b, T& ia, T& ib) {
+  ia = drcp(a);
+  ib = drcp(b);
+}
+// Floor that keeps a sum of non-negative terms which rounds to zero or below
+// off the poles of the routines above.
+template <class T> __host__ __device__ __forceinline__ T tiny_positive() { return T(1e-290); }
+template <> __host__ __device__ __forceinline__ float tiny_positive<float>() { return 1e-36f; }
+
+// Smaller and larger of two values (one instruction each on the device).
+template <class T> __host__ __device__ __forceinline__ T pmin(T a, T b) { return b < a ? b : a; }
+template <class T> __host__ __device__ __forceinline__ T pmax(T a, T b) { return a < b ? b : a; }
+__device__ __forceinline__ double pmin(double a, double b) { return __builtin_fmin(a, b); }
+__device__ __forceinline__ double pmax(double a, double b) { return __builtin_fmax(a, b); }
+__device__ __forceinline__ float pmin(float a, float b) { return __builtin_fminf(a, b); }
+__device__ __forceinline__ float pmax(float a, float b) { return __builtin_fmaxf(a, b); }
+__host__ __forceinline__ double pmin(double a, double b) { return b < a ? b : a; }
+__host__ __forceinline__ double pmax(double a, double b) { return a < b ? b : a; }
+__host__ __forceinline__ float pmin(float a, float b) { return b < a ? b : a; }
+__host__ __forceinline__ float pmax(float a, float b) { return a < b ? b : a; }
+
 // minmod limiter: 0 when the one-sided differences disagree in sign (or one
-// is zero), else the one of smaller magnitude (a on ties).
+// is zero), else the one of smaller magnitude (a on ties).  That is the
+// median of a, b and 0: one instruction in float on the device, four minima
+// and maxima in double, against seven (compares, a product, and two selects)
+// spelled out; 24 of them a cell.
 template <class T> __host__ __device__ __forceinline__ T limiter_minmod(T a, T b) {
   T r = (dabs(b) < dabs(a)) ? b : a;
   return (a * b > T(0)) ? r : T(0);
 }
+__device__ __forceinline__ double limiter_minmod(double a, double b) {
+  return pmax(pmin(a, b), pmin(pmax(a, b), 0.0));
+}
+__device__ __forceinline__ float limiter_minmod(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, 0.0f); }
+__host__ __forceinline__ double limiter_minmod(double a, double b) { return pmax(pmin(a, b), pmin(pmax(a, b), 0.0)); }
+__host__ __forceinline__ float limiter_minmod(float a, float b) { return pmax(pmin(a, b), pmin(pmax(a, b), 0.0f)); }
 
 // W -> U for one state.
 template <class T> __host__ __device__ __forceinline__ void to_conserved(const T (&w)[8], T (&u)[8], T gm1_inv) {
@@ -92,49 +173,56 @@ template <class T> __host__ __device__ __forceinline__ void to_conserved(const T
   u[1] = w[0] * w[1];
   u[2] = w[0] * w[2];
   u[3] = w[0] * w[3];
-  T v2 = w[1] * w[1] + w[2] * w[2] + w[3] * w[3];
   T b2 = w[5] * w[5] + w[6] * w[6] + w[7] * w[7];
-  u[4] = w[4] * gm1_inv + T(0.5) * w[0] * v2 + T(0.5) * b2;
+  u[4] = w[4] * gm1_inv + T(0.5) * (b2 + u[1] * w[1] + u[2] * w[2] + u[3] * w[3]);
   u[5] = w[5];
   u[6] = w[6];
   u[7] = w[7];
 }
 
-// U -> W for one state.
-template <class T> __host__ __device__ __forceinline__ void to_primitive(const T (&u)[8], T (&w)[8], T gm1) {
-  T ir = drcp(u[0]);
+// U -> W for one state, given 1 / rho.
+template <class T>
+__host__ __device__ __forceinline__ void to_primitive_ir(const T (&u)[8], T (&w)[8], T gm1, T ir) {
   w[0] = u[0];
   w[1] = u[1] * ir;
   w[2] = u[2] * ir;
   w[3] = u[3] * ir;
-  T v2 = w[1] * w[1] + w[2] * w[2] + w[3] * w[3];
   T b2 = u[5] * u[5] + u[6] * u[6] + u[7] * u[7];
-  w[4] = gm1 * (u[4] - T(0.5) * u[0] * v2 - T(0.5) * b2);
+  w[4] = gm1 * (u[4] - T(0.5) * (b2 + u[1] * w[1] + u[2] * w[2] + u[3] * w[3]));
   w[5] = u[5];
   w[6] = u[6];
   w[7] = u[7];
 }
+// U -> W for one state.
+template <class T> __host__ __device__ __forceinline__ void to_primitive(const T (&u)[8], T (&w)[8], T gm1) {
+  to_primitive_ir(u, w, gm1, drcp(u[0]));
+}
 
-// Physical flux along lab axis D of primitive w (8 components, F(B_D) = 0).
+// Physical flux along lab axis D of primitive w and its conserved state u
+// (8 components, F(B_D) = 0).
 template <int D, class T>
-__host__ __device__ __forceinline__ void flux_along(const T (&w)[8], T (&f)[8], T gm1_inv) {
-  const T r = w[0];
+__host__ __device__ __forceinline__ void flux_along(const T (&w)[8], const T (&u)[8], T (&f)[8]) {
   const T vn = w[1 + D];
   const T bn = w[5 + D];
-  T v2 = w[1] * w[1] + w[2] * w[2] + w[3] * w[3];
   T b2 = w[5] * w[5] + w[6] * w[6] + w[7] * w[7];
   T pt = w[4] + T(0.5) * b2;
-  T e = w[4] * gm1_inv + T(0.5) * r * v2 + T(0.5) * b2;
   T vb = w[1] * w[5] + w[2] * w[6] + w[3] * w[7];
-  T rvn = r * vn;
+  const T rvn = u[1 + D];
   f[0] = rvn;
 #pragma unroll
   for (int a = 0; a < 3; ++a) f[1 + a] = rvn * w[1 + a] - bn * w[5 + a];
   f[1 + D] += pt;
-  f[4] = (e + pt) * vn - bn * vb;
+  f[4] = (u[4] + pt) * vn - bn * vb;
 #pragma unroll
   for (int a = 0; a < 3; ++a) f[5 + a] = w[5 + a] * vn - bn * w[1 + a];
   f[5 + D] = T(0);
+}
+// The same from the primitive state alone.
+template <int D, class T>
+__host__ __device__ __forceinline__ void flux_along(const T (&w)[8], T (&f)[8], T gm1_inv) {
+  T u[8];
+  to_conserved(w, u, gm1_inv);
+  flux_along<D>(w, u, f);
 }
 
 // Fast magnetosonic speed for density r, pressure p, |B|^2 = b2 and the field
@@ -149,166 +237,148 @@ template <class T> __host__ __device__ __forceinline__ T fast_magnetosonic(T r, 
 
 // HLLD flux (Miyoshi & Kusano 2005).  Inputs in the rotated frame:
 // q = (rho, un, ut1, ut2, p, [unused], bt1, bt2); bn shared.  Output
-// f = (rho, m_n, m_t1, m_t2, E, B_t1, B_t2).  Evaluated without early exits:
-// every intermediate state is formed and the flux of the region that
-// contains x/t = 0 is selected at the end (first true test of S_L > 0,
-// S*_L >= 0, S_M >= 0, S*_R >= 0, S_R >= 0; else the right state).
+// f = (rho, m_n, m_t1, m_t2, E, B_t1, B_t2).  The region that contains
+// x/t = 0 is the first true test of S_L > 0, S*_L >= 0, S_M >= 0, S*_R >= 0,
+// S_R >= 0 (else the right state).  The star states satisfy the jump
+// conditions with the total pressure and normal velocity they share, so the
+// flux of every region is the physical flux of its state, evaluated once:
+// the inner (double-star) state of the chosen side, which subsonic and
+// sub-Alfvenic flow is in, or under a branch that few waves take the star or
+// the outer state.  Against forming every state and the jumps
+// F + S (U* - U) + S* (U** - U*) with selects between both sides this is
+// about 240 instead of 430 vector instructions in double (a select of a
+// double is two), and the kernels here are bound by their issue.
 template <class T>
-__host__ __device__ __forceinline__ void riemann_hlld(const T (&ql)[8], const T (&qr)[8], T bn, T gam, T (&f)[7]) {
-  const T gm1_inv = drcp(gam - T(1));
+__host__ __device__ __forceinline__ void riemann_hlld(const T (&ql)[8], const T (&qr)[8], T bn, T gam, T gm1_inv,
+                                                      T (&f)[7]) {
   const T bn2 = bn * bn;
 
   // Left / right totals.
-  T b2l = bn2 + ql[6] * ql[6] + ql[7] * ql[7];
-  T b2r = bn2 + qr[6] * qr[6] + qr[7] * qr[7];
-  T ptl = ql[4] + T(0.5) * b2l;
-  T ptr = qr[4] + T(0.5) * b2r;
-  T el = ql[4] * gm1_inv + T(0.5) * ql[0] * (ql[1] * ql[1] + ql[2] * ql[2] + ql[3] * ql[3]) + T(0.5) * b2l;
-  T er = qr[4] * gm1_inv + T(0.5) * qr[0] * (qr[1] * qr[1] + qr[2] * qr[2] + qr[3] * qr[3]) + T(0.5) * b2r;
+  const T b2l = bn2 + ql[6] * ql[6] + ql[7] * ql[7];
+  const T b2r = bn2 + qr[6] * qr[6] + qr[7] * qr[7];
+  const T ptl = ql[4] + T(0.5) * b2l;
+  const T ptr = qr[4] + T(0.5) * b2r;
 
-  T cfl = fast_magnetosonic(ql[0], ql[4], b2l, bn, gam);
-  T cfr = fast_magnetosonic(qr[0], qr[4], b2r, bn, gam);
-  T cmx = cfl > cfr ? cfl : cfr;
-  T sl = (ql[1] < qr[1] ? ql[1] : qr[1]) - cmx;
-  T sr = (ql[1] > qr[1] ? ql[1] : qr[1]) + cmx;
+  // Larger fast speed: c^2 = (A + sqrt(A^2 - 4 gamma p bn^2)) / (2 rho) with
+  // A = gamma p + B^2; the sides' c^2 are compared before the root.
+  const T bn4 = T(4) * bn2;
+  const T gpl = gam * ql[4], gpr = gam * qr[4];
+  const T al = gpl + b2l, ar = gpr + b2r;
+  const T tp = tiny_positive<T>();
+  T sdl, sdr, unused;
+  sqrt_rsqrt(pmax(al * al - gpl * bn4, tp), sdl, unused);
+  sqrt_rsqrt(pmax(ar * ar - gpr * bn4, tp), sdr, unused);
+  const T zl = pmax(al + sdl, tp), zr = pmax(ar + sdr, tp);
+  const bool lmax = zl * qr[0] > zr * ql[0];
+  const T cmx = sqrt_ratio(T(0.5) * (lmax ? zl : zr), lmax ? ql[0] : qr[0]);
+  const T sl = pmin(ql[1], qr[1]) - cmx;
+  const T sr = pmax(ql[1], qr[1]) + cmx;
 
   // Contact speed and star total pressure.
-  T dl = sl - ql[1];
-  T dr = sr - qr[1];
-  T rdl = ql[0] * dl;
-  T rdr = qr[0] * dr;
-  T sm = (rdr * qr[1] - rdl * ql[1] - ptr + ptl) * drcp(rdr - rdl);
-  T pts = ptl + rdl * (sm - ql[1]);
+  const T dl = sl - ql[1];
+  const T dr = sr - qr[1];
+  const T rdl = ql[0] * dl;
+  const T rdr = qr[0] * dr;
+  const T sm = (rdr * qr[1] - rdl * ql[1] - ptr + ptl) * drcp(rdr - rdl);
+  const T tl = sm - ql[1], tr = sm - qr[1];
+  const T pts = ptl + rdl * tl;
   const T tiny = T(1e-12) * pts;
 
-  // Outer star states: density, tangential v and B, energy.
-  T rsl, vsl, wsl, bysl, bzsl, esl;
-  T rsr, vsr, wsr, bysr, bzsr, esr;
+  // Outer star states: density, tangential v and B, energy.  With
+  // g = (S_M - u) / (rho (S - u)(S - S_M) - bn^2) the tangential fields are
+  // v* = v - bt bn g and bt* = bt (1 + rho (S - u) g); g = 0 (v and bt kept)
+  // where that denominator is degenerate.
+  T rsl, vsl, wsl, bysl, bzsl, vbsl, esl;
   {
-    T dsm = sl - sm;
-    T idsm = drcp(dsm);
+    const T dsm = sl - sm;
+    const T den = rdl * dsm - bn2;
+    const bool deg = dabs(den) <= tiny;
+    T idsm, iden;
+    drcp2(dsm, deg ? T(1) : den, idsm, iden);
+    const T g = deg ? T(0) : tl * iden;
     rsl = rdl * idsm;
-    T den = rdl * dsm - bn2;
-    bool deg = dabs(den) <= tiny;
-    T iden = deg ? T(0) : drcp(den);
-    T fv = bn * (sm - ql[1]) * iden;
-    T fb = (rdl * dl - bn2) * iden;
-    vsl = deg ? ql[2] : ql[2] - ql[6] * fv;
-    wsl = deg ? ql[3] : ql[3] - ql[7] * fv;
-    bysl = deg ? ql[6] : ql[6] * fb;
-    bzsl = deg ? ql[7] : ql[7] * fb;
-    T vb = ql[1] * bn + ql[2] * ql[6] + ql[3] * ql[7];
-    T vbs = sm * bn + vsl * bysl + wsl * bzsl;
-    esl = (dl * el - ptl * ql[1] + pts * sm + bn * (vb - vbs)) * idsm;
+    const T fv = bn * g, fb = T(1) + rdl * g;
+    vsl = ql[2] - ql[6] * fv;
+    wsl = ql[3] - ql[7] * fv;
+    bysl = ql[6] * fb;
+    bzsl = ql[7] * fb;
+    const T vb = ql[1] * bn + ql[2] * ql[6] + ql[3] * ql[7];
+    vbsl = sm * bn + vsl * bysl + wsl * bzsl;
+    const T e = ql[4] * gm1_inv + T(0.5) * (ql[0] * (ql[1] * ql[1] + ql[2] * ql[2] + ql[3] * ql[3]) + b2l);
+    esl = (dl * e - ptl * ql[1] + pts * sm + bn * (vb - vbsl)) * idsm;
   }
+  T rsr, vsr, wsr, bysr, bzsr, vbsr, esr;
   {
-    T dsm = sr - sm;
-    T idsm = drcp(dsm);
+    const T dsm = sr - sm;
+    const T den = rdr * dsm - bn2;
+    const bool deg = dabs(den) <= tiny;
+    T idsm, iden;
+    drcp2(dsm, deg ? T(1) : den, idsm, iden);
+    const T g = deg ? T(0) : tr * iden;
     rsr = rdr * idsm;
-    T den = rdr * dsm - bn2;
-    bool deg = dabs(den) <= tiny;
-    T iden = deg ? T(0) : drcp(den);
-    T fv = bn * (sm - qr[1]) * iden;
-    T fb = (rdr * dr - bn2) * iden;
-    vsr = deg ? qr[2] : qr[2] - qr[6] * fv;
-    wsr = deg ? qr[3] : qr[3] - qr[7] * fv;
-    bysr = deg ? qr[6] : qr[6] * fb;
-    bzsr = deg ? qr[7] : qr[7] * fb;
-    T vb = qr[1] * bn + qr[2] * qr[6] + qr[3] * qr[7];
-    T vbs = sm * bn + vsr * bysr + wsr * bzsr;
-    esr = (dr * er - ptr * qr[1] + pts * sm + bn * (vb - vbs)) * idsm;
+    const T fv = bn * g, fb = T(1) + rdr * g;
+    vsr = qr[2] - qr[6] * fv;
+    wsr = qr[3] - qr[7] * fv;
+    bysr = qr[6] * fb;
+    bzsr = qr[7] * fb;
+    const T vb = qr[1] * bn + qr[2] * qr[6] + qr[3] * qr[7];
+    vbsr = sm * bn + vsr * bysr + wsr * bzsr;
+    const T e = qr[4] * gm1_inv + T(0.5) * (qr[0] * (qr[1] * qr[1] + qr[2] * qr[2] + qr[3] * qr[3]) + b2r);
+    esr = (dr * e - ptr * qr[1] + pts * sm + bn * (vb - vbsr)) * idsm;
   }
 
   // Alfven speeds and the inner (double-star) state.
-  T sql = psqrt(rsl);
-  T sqr = psqrt(rsr);
-  T abn = dabs(bn);
-  T ssl = sm - abn * drcp(sql);
-  T ssr = sm + abn * drcp(sqr);
-  bool ddeg = T(0.5) * bn2 <= tiny;
-  T sg = bn > T(0) ? T(1) : T(-1);
-  T isum = drcp(sql + sqr);
-  T vss = (sql * vsl + sqr * vsr + (bysr - bysl) * sg) * isum;
-  T wss = (sql * wsl + sqr * wsr + (bzsr - bzsl) * sg) * isum;
-  T byss = (sql * bysr + sqr * bysl + sql * sqr * (vsr - vsl) * sg) * isum;
-  T bzss = (sql * bzsr + sqr * bzsl + sql * sqr * (wsr - wsl) * sg) * isum;
-  T vbss = sm * bn + vss * byss + wss * bzss;
-  T essl = esl - sql * (sm * bn + vsl * bysl + wsl * bzsl - vbss) * sg;
-  T essr = esr + sqr * (sm * bn + vsr * bysr + wsr * bzsr - vbss) * sg;
-  if (ddeg) {
-    vss = vsl; wss = wsl; byss = bysl; bzss = bzsl; essl = esl;
+  T sql, sqr, isql, isqr;
+  sqrt_rsqrt(rsl, sql, isql);
+  sqrt_rsqrt(rsr, sqr, isqr);
+  const T abn = dabs(bn);
+  const T ssl = sm - abn * isql;
+  const T ssr = sm + abn * isqr;
+  const T sg = bn > T(0) ? T(1) : T(-1);
+  const T isum = drcp(sql + sqr);
+  const T ssg = sql * sqr * sg;
+  const bool left = sm >= T(0) || sl > T(0);
+  T vb = sm * bn;
+  T v = (sql * vsl + sqr * vsr + (bysr - bysl) * sg) * isum;
+  T w = (sql * wsl + sqr * wsr + (bzsr - bzsl) * sg) * isum;
+  T by = (sql * bysr + sqr * bysl + ssg * (vsr - vsl)) * isum;
+  T bz = (sql * bzsr + sqr * bzsl + ssg * (wsr - wsl)) * isum;
+  vb = vb + v * by + w * bz;
+  T u = sm, pt = pts;
+  T r = left ? rsl : rsr;
+  T e = left ? esl - sql * sg * (vbsl - vb) : esr + sqr * sg * (vbsr - vb);
+
+  // The inner state holds x/t = 0 unless a test before it does or the normal
+  // field is degenerate (the inner states then equal the star states).
+  const bool inner = (left ? !(sl > T(0)) && !(ssl >= T(0)) : ssr >= T(0)) && !(T(0.5) * bn2 <= tiny);
+  if (!inner) {
+    v = left ? vsl : vsr;
+    w = left ? wsl : wsr;
+    by = left ? bysl : bysr;
+    bz = left ? bzsl : bzsr;
+    vb = left ? vbsl : vbsr;
+    e = left ? esl : esr;
+    // the outer state beyond the fast waves; where the inner states are
+    // degenerate and the star region is passed over, the star state stands
+    if (left ? sl > T(0) : !(ssr >= T(0)) && !(sr >= T(0))) {
+      r = left ? ql[0] : qr[0];
+      u = left ? ql[1] : qr[1];
+      v = left ? ql[2] : qr[2];
+      w = left ? ql[3] : qr[3];
+      by = left ? ql[6] : qr[6];
+      bz = left ? ql[7] : qr[7];
+      pt = left ? ptl : ptr;
+      vb = u * bn + v * by + w * bz;
+      e = (left ? ql[4] : qr[4]) * gm1_inv + T(0.5) * (r * (u * u + v * v + w * w) + (left ? b2l : b2r));
+    }
   }
-  // (the right double-star state equals the right star state when degenerate)
-  T vssr = ddeg ? vsr : vss, wssr = ddeg ? wsr : wss, byssr = ddeg ? bysr : byss, bzssr = ddeg ? bzsr : bzss;
-  T essr2 = ddeg ? esr : essr;
-
-  // Region choice.
-  int region;
-  if (sl > T(0)) region = 0;
-  else if (ssl >= T(0)) region = 1;
-  else if (sm >= T(0)) region = 2;
-  else if (ssr >= T(0)) region = 3;
-  else if (sr >= T(0)) region = 4;
-  else region = 5;
-
-  // Base: physical flux of the outer state of the chosen side, then the
-  // jumps F* = F + S (U* - U) and F** = F* + S* (U** - U*).
-  const bool left = region <= 2;
-  const T r0 = left ? ql[0] : qr[0];
-  const T u0 = left ? ql[1] : qr[1];
-  const T v0 = left ? ql[2] : qr[2];
-  const T w0 = left ? ql[3] : qr[3];
-  const T by0 = left ? ql[6] : qr[6];
-  const T bz0 = left ? ql[7] : qr[7];
-  const T e0 = left ? el : er;
-  const T pt0 = left ? ptl : ptr;
-  T vb0 = u0 * bn + v0 * by0 + w0 * bz0;
-  T ru = r0 * u0;
-  f[0] = ru;
-  f[1] = ru * u0 + pt0 - bn2;
-  f[2] = ru * v0 - bn * by0;
-  f[3] = ru * w0 - bn * bz0;
-  f[4] = (e0 + pt0) * u0 - bn * vb0;
-  f[5] = by0 * u0 - bn * v0;
-  f[6] = bz0 * u0 - bn * w0;
-  if (region == 0 || region == 5) return;
-
-  const T s = left ? sl : sr;
-  const T rs = left ? rsl : rsr;
-  const T vs = left ? vsl : vsr;
-  const T ws = left ? wsl : wsr;
-  const T bys = left ? bysl : bysr;
-  const T bzs = left ? bzsl : bzsr;
-  const T es = left ? esl : esr;
-  // U* - U (7 components)
-  T j0 = rs - r0;
-  T j1 = rs * sm - ru;
-  T j2 = rs * vs - r0 * v0;
-  T j3 = rs * ws - r0 * w0;
-  T j4 = es - e0;
-  T j5 = bys - by0;
-  T j6 = bzs - bz0;
-  f[0] += s * j0;
-  f[1] += s * j1;
-  f[2] += s * j2;
-  f[3] += s * j3;
-  f[4] += s * j4;
-  f[5] += s * j5;
-  f[6] += s * j6;
-  if (region == 1 || region == 4) return;
-
-  const T ss = left ? ssl : ssr;
-  const T vss2 = left ? vss : vssr;
-  const T wss2 = left ? wss : wssr;
-  const T byss2 = left ? byss : byssr;
-  const T bzss2 = left ? bzss : bzssr;
-  const T ess2 = left ? essl : essr2;
-  // U** - U* (density and normal momentum unchanged)
-  f[2] += ss * (rs * (vss2 - vs));
-  f[3] += ss * (rs * (wss2 - ws));
-  f[4] += ss * (ess2 - es);
-  f[5] += ss * (byss2 - bys);
-  f[6] += ss * (bzss2 - bzs);
+  f[0] = r * u;
+  f[1] = f[0] * u + (pt - bn2);
+  f[2] = f[0] * v - bn * by;
+  f[3] = f[0] * w - bn * bz;
+  f[4] = (e + pt) * u - bn * vb;
+  f[5] = by * u - bn * v;
+  f[6] = bz * u - bn * w;
 }
 
 }  // namespace amr

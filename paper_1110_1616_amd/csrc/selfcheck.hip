@@ -133,7 +133,7 @@ double amr_selfcheck_adjoint(int32_t which, int32_t ntrials, uint64_t seed) {
           ql[q] = xx[q];
           qr[q] = xx[8 + q];
         }
-        riemann_hlld(ql, qr, xx[16], gam, f);
+        riemann_hlld(ql, qr, xx[16], gam, gi, f);
         for (int q = 0; q < 7; ++q) out[q] = f[q];
       }
     };
@@ -170,7 +170,7 @@ double amr_selfcheck_adjoint(int32_t which, int32_t ntrials, uint64_t seed) {
           ql[q] = xd[q];
           qr[q] = xd[8 + q];
         }
-        riemann_hlld(ql, qr, xd[16], HDual(gam), f);
+        riemann_hlld(ql, qr, xd[16], HDual(gam), HDual(gi), f);
         for (int q = 0; q < 7; ++q) od[q] = f[q];
       }
       for (int i = 0; i < nout; ++i) fd += lam[i] * od[i].d;
