@@ -121,11 +121,11 @@ __global__ __launch_bounds__(256) void k_adj_pred(const GridDesc* __restrict__ g
     fb[2][0] = NDIM == 3 ? U.f[7][p.e] : T(0);
     fb[2][1] = NDIM == 3 ? U.f[7][p.e + st[2]] : T(0);
     Pred<T, NDIM> pr;
-    T dzm[8], dzp[8];
+    T dzm[8], dzp[8], du[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) { dzm[q] = w[q] - wzm[q]; dzp[q] = wzp[q] - w[q]; }
     const T hcdt[3] = {ls.hdt * ls.idx[0], ls.hdt * ls.idx[1], ls.hdt * ls.idx[2]};
-    (void)predict<T, NDIM>(w, wxm, wxp, wym, wyp, dzm, dzp, fb, hcdt, gm1, gm1_inv, pr);
+    (void)predict<T, NDIM>(w, wxm, wxp, wym, wyp, dzm, dzp, fb, hcdt, gm1, gm1_inv, pr, du);
 #pragma unroll
     for (int d = 0; d < NDIM; ++d)
 #pragma unroll

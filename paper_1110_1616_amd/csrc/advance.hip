@@ -133,10 +133,9 @@ __global__ __launch_bounds__(256) void k_flux(const GridDesc* __restrict__ grids
           wyp[q] = sW[q][eo + kW];
         }
         if ((wcur[0] <= T(0)) || (wcur[4] <= T(0))) flag_bad(err, ix(cx, cy, k));
-        bool ok;
+        T du[8];
+        const bool ok = predict<T, NDIM>(wcur, wxm, wxp, wym, wyp, dzm, dzp, fbcur, hcdt, gm1, gm1_inv, pr, du);
         if constexpr (UPWIND) {
-          T du[8];
-          ok = predict_du<T, NDIM>(wcur, wxm, wxp, wym, wyp, dzm, dzp, fbcur, hcdt, gm1, gm1_inv, pr, du);
           // reference EMF of the upwinded CT: -v x B with v of the half-step
           // cell state U + du and B at time n; one writer per cell (the
           // tile's own cells, plus the grid's first column / row / plane)
@@ -152,8 +151,6 @@ __global__ __launch_bounds__(256) void k_flux(const GridDesc* __restrict__ grids
             }
             stb(F.e[2], eb, vy * wcur[5] - vx * wcur[6]);
           }
-        } else {
-          ok = predict<T, NDIM>(wcur, wxm, wxp, wym, wyp, dzm, dzp, fbcur, hcdt, gm1, gm1_inv, pr);
         }
         if (!ok) flag_bad(err, ix(cx, cy, k));
 #pragma unroll
@@ -271,15 +268,17 @@ __global__ __launch_bounds__(256) void k_update(const GridDesc* __restrict__ gri
         for (int s = 0; s < 5; ++s) {
           // lab conserved slot s -> rotated component of each direction
           const int qx = hydro_comp(s, 0), qy = hydro_comp(s, 1), qz = hydro_comp(s, 2);
-          const T acc = flux_delta<T, NDIM>(cdx, F.f[0][qx][e + 1], F.f[0][qx][e], cdy, F.f[1][qy][e + st[1]],
-                                            F.f[1][qy][e], cdz, NDIM == 3 ? F.f[2][qz][e + st[2]] : T(0),
-                                            NDIM == 3 ? F.f[2][qz][e] : T(0));
+          const T xh = F.f[0][qx][e + 1], xl = F.f[0][qx][e], yh = F.f[1][qy][e + st[1]], yl = F.f[1][qy][e];
+          T acc;
+          if constexpr (NDIM == 3)
+            acc = add_high(flux_low(cdx, xh, xl, cdy, yh, yl, cdz, F.f[2][qz][e]), cdz, F.f[2][qz][e + st[2]]);
+          else
+            acc = flux_delta2(cdx, xh, xl, cdy, yh, yl);
           Uout.f[s][e] = Uin.f[s][e] - acc;
         }
         if (NDIM == 2) {
           // cell-centred Bz: x-flux component t2 (index 6), y-flux component t1 (index 5)
-          const T acc = flux_delta<T, 2>(cdx, F.f[0][6][e + 1], F.f[0][6][e], cdy, F.f[1][5][e + st[1]],
-                                         F.f[1][5][e], T(0), T(0), T(0));
+          const T acc = flux_delta2(cdx, F.f[0][6][e + 1], F.f[0][6][e], cdy, F.f[1][5][e + st[1]], F.f[1][5][e]);
           Uout.f[7][e] = Uin.f[7][e] - acc;
         }
       }
@@ -288,12 +287,12 @@ __global__ __launch_bounds__(256) void k_update(const GridDesc* __restrict__ gri
         if (cy < uhy && k < uhz) {  // Bx face (cx, cy, k)
           T ez0 = emf_at<2, UPWIND>(F, e, st), ez1 = emf_at<2, UPWIND>(F, e + st[1], st);
           T ey0 = emf_at<1, UPWIND>(F, e, st), ey1 = emf_at<1, UPWIND>(F, e + st[2], st);
-          Uout.f[5][e] = Uin.f[5][e] - curl_delta(cdy, ez1, ez0, cdz, ey1, ey0);
+          Uout.f[5][e] = Uin.f[5][e] - add_high(curl_low(cdy, ez1, ez0, cdz, ey0), -cdz, ey1);
         }
         if (cx < uhx && k < uhz) {  // By face
           T ex0 = emf_at<0, UPWIND>(F, e, st), ex1 = emf_at<0, UPWIND>(F, e + st[2], st);
           T ez0 = emf_at<2, UPWIND>(F, e, st), ez1 = emf_at<2, UPWIND>(F, e + st[0], st);
-          Uout.f[6][e] = Uin.f[6][e] - curl_delta(cdz, ex1, ex0, cdx, ez1, ez0);
+          Uout.f[6][e] = Uin.f[6][e] - add_high(curl_low(-cdx, ez1, ez0, -cdz, ex0), cdz, ex1);
         }
         if (cx < uhx && cy < uhy) {  // Bz face
           T ey0 = emf_at<1, UPWIND>(F, e, st), ey1 = emf_at<1, UPWIND>(F, e + st[0], st);

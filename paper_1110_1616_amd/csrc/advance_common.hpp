@@ -180,29 +180,22 @@ struct Pred {
   T p[3][7];  // high-side (plus) states per direction
 };
 
-// Slopes, face states, Hancock increment and predicted states of one cell.
-// wx/wy hold the neighbours (minus, plus) along x and y, dzm and dzp the
-// differences to the cell below and above (a kernel marching along z has
+// Limited slopes of one cell and the Hancock increment of its conserved
+// state.  wx/wy hold the neighbours (minus, plus) along x and y, dzm and dzp
+// the differences to the cell below and above (a kernel marching along z has
 // formed dzm as the last plane's dzp); fb[d][0/1] are the cell's low/high
-// face fields along d, hcdt[d] half dt / dx_d.  Each pair of predicted states
-// of a direction is handed to emit(d, low, high) as soon as it is formed, so
-// callers that store it right away never hold all 2*NDIM states in
-// registers.  Returns false if a predicted density or pressure is not
-// positive.  When WANT_DU, du_out receives the Hancock increment of the
-// cell's conserved state.
-template <class T, int NDIM, bool WANT_DU = false, class Emit>
-__device__ __forceinline__ bool predict_emit(const T (&w)[8], const T (&wxm)[8], const T (&wxp)[8],
-                                             const T (&wym)[8], const T (&wyp)[8], const T (&dzm)[8],
-                                             const T (&dzp)[8], const T (&fb)[3][2], const T (&hcdt)[3], T gm1,
-                                             T gm1_inv, Emit&& emit, T (&du_out)[8]) {
-  T sl[3][8];
+// face fields along d, hcdt[d] half dt / dx_d.
+template <class T, int NDIM>
+__device__ __forceinline__ void hancock_slopes(const T (&w)[8], const T (&wxm)[8], const T (&wxp)[8],
+                                               const T (&wym)[8], const T (&wyp)[8], const T (&dzm)[8],
+                                               const T (&dzp)[8], const T (&fb)[3][2], const T (&hcdt)[3], T gm1_inv,
+                                               T (&sl)[3][8], T (&du)[8]) {
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
     sl[0][q] = limiter_minmod(w[q] - wxm[q], wxp[q] - w[q]);
     sl[1][q] = limiter_minmod(w[q] - wym[q], wyp[q] - w[q]);
-    if (NDIM == 3) sl[2][q] = limiter_minmod(dzm[q], dzp[q]);
+    sl[2][q] = NDIM == 3 ? limiter_minmod(dzm[q], dzp[q]) : T(0);
   }
-  T du[8];
 #pragma unroll
   for (int q = 0; q < 8; ++q) du[q] = T(0);
 #pragma unroll
@@ -228,10 +221,16 @@ __device__ __forceinline__ bool predict_emit(const T (&w)[8], const T (&wxm)[8],
 #pragma unroll
     for (int q = 0; q < 8; ++q) du[q] -= hcdt[d] * (fr[q] - fl[q]);
   }
-  if constexpr (WANT_DU) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) du_out[q] = du[q];
-  }
+}
+
+// Predicted face states of one cell from its slopes and increment.  Each pair
+// of a direction is handed to emit(d, low, high) as soon as it is formed, so
+// callers that store it right away never hold all 2*NDIM states in
+// registers.  Returns false if a predicted density or pressure is not
+// positive.
+template <class T, int NDIM, class Emit>
+__device__ __forceinline__ bool hancock_states(const T (&w)[8], const T (&sl)[3][8], const T (&du)[8],
+                                               const T (&fb)[3][2], T gm1, T gm1_inv, Emit&& emit) {
   bool ok = true;
 #pragma unroll
   for (int d = 0; d < NDIM; ++d) {
@@ -262,36 +261,21 @@ __device__ __forceinline__ bool predict_emit(const T (&w)[8], const T (&wxm)[8],
   return ok;
 }
 
+// Both, the increment returned too.
 template <class T, int NDIM>
 __device__ __forceinline__ bool predict(const T (&w)[8], const T (&wxm)[8], const T (&wxp)[8], const T (&wym)[8],
                                         const T (&wyp)[8], const T (&dzm)[8], const T (&dzp)[8],
                                         const T (&fb)[3][2], const T (&hcdt)[3], T gm1, T gm1_inv,
-                                        Pred<T, NDIM>& out) {
-  T unused[8];
-  return predict_emit<T, NDIM>(w, wxm, wxp, wym, wyp, dzm, dzp, fb, hcdt, gm1, gm1_inv,
-                               [&](int d, const T (&lo)[7], const T (&hi)[7]) {
+                                        Pred<T, NDIM>& out, T (&du)[8]) {
+  T sl[3][8];
+  hancock_slopes<T, NDIM>(w, wxm, wxp, wym, wyp, dzm, dzp, fb, hcdt, gm1_inv, sl, du);
+  return hancock_states<T, NDIM>(w, sl, du, fb, gm1, gm1_inv, [&](int d, const T (&lo)[7], const T (&hi)[7]) {
 #pragma unroll
-                                 for (int c = 0; c < 7; ++c) {
-                                   out.m[d][c] = lo[c];
-                                   out.p[d][c] = hi[c];
-                                 }
-                               }, unused);
-}
-
-// predict() that also returns the Hancock increment du of the cell.
-template <class T, int NDIM>
-__device__ __forceinline__ bool predict_du(const T (&w)[8], const T (&wxm)[8], const T (&wxp)[8], const T (&wym)[8],
-                                           const T (&wyp)[8], const T (&dzm)[8], const T (&dzp)[8],
-                                           const T (&fb)[3][2], const T (&hcdt)[3], T gm1, T gm1_inv,
-                                           Pred<T, NDIM>& out, T (&du)[8]) {
-  return predict_emit<T, NDIM, true>(w, wxm, wxp, wym, wyp, dzm, dzp, fb, hcdt, gm1, gm1_inv,
-                                     [&](int d, const T (&lo)[7], const T (&hi)[7]) {
-#pragma unroll
-                                       for (int c = 0; c < 7; ++c) {
-                                         out.m[d][c] = lo[c];
-                                         out.p[d][c] = hi[c];
-                                       }
-                                     }, du);
+    for (int c = 0; c < 7; ++c) {
+      out.m[d][c] = lo[c];
+      out.p[d][c] = hi[c];
+    }
+  });
 }
 
 template <class T>

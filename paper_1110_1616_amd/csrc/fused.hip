@@ -4,15 +4,14 @@
 // update) in one launch, so the face fluxes never travel through HBM.
 //
 // A work item is a column tile of tw x th threads over cells
-// (x0-1+tx, y0-1+ty) marching along z.  Per plane k every active lane forms
-// its cell's predicted face states; lanes then solve the Riemann problems of
-// their cell's low x-face (tx >= 1), low y-face (ty >= 1) and low z-face
-// (from the state carried from plane k-1), and the fluxes go to LDS, double
-// buffered over two planes.  From them come the edge EMFs E_z of plane k and
-// E_x, E_y at z = k - 1/2, and the update of plane k-1 (cells and their x-
-// and y-faces) and of the z-faces at k - 1/2.  A plane takes two barriers in
-// 3-D: the update reads E_z of the plane below (from the iteration before)
-// and forms the neighbours' E_x, E_y again from their inputs in LDS.  A tile updates the cells of
+// (x0-1+tx, y0-1+ty) marching along z.  Per plane k every lane forms its
+// cell's predicted face states and solves the Riemann problems of the cell's
+// low x-, y- and z-face (the z one from the state carried from plane k-1);
+// the fluxes go to LDS, where the face states were, and from them come the
+// edge EMFs E_z of plane k and E_x, E_y at z = k - 1/2 of the lane and of its
+// neighbours, the update of plane k-1 (cells and their x- and y-faces) and
+// of the z-faces at k - 1/2.  What plane k's update needs of its own fluxes
+// is carried as one value a field.  A tile updates the cells of
 // lanes tx in [1, tw-2], ty in [1, th-2] (their high faces and the edges
 // around them are computed in the tile); tiles overlap by two columns and
 // rows (the last x- and y-face of the update region go to the lane that
@@ -21,6 +20,21 @@
 // emf.hpp), and the library is compiled with multiply-add contraction
 // inside single expressions only, so the results equal the two-kernel
 // path's bit for bit.
+//
+// What bounds it: instruction issue.  A plane takes about 1840 vector and
+// 450 other instructions a wave in FP64; a wave alone on its SIMD issues at
+// most one of any kind every four cycles and waits for LDS, barriers and
+// dependent FP64 results in between, so two waves share each SIMD: 256
+// registers and 75 KB of LDS a block in FP64, two blocks a CU (150 registers
+// in FP32, three).  To fit, the z differences wait in LDS, W of the next
+// plane is read back from the W plane, and the loads of the next planes are
+// issued behind the Riemann problems instead of a plane ahead.  Against one
+// block a CU with 375 registers, 115 KB and the loads a plane ahead: two
+// steps of a 128^3 grid 770 -> 628 us, two coarse steps of the 549-grid
+// hierarchy 6225 -> 5442 us (FP32: the same within 1%).  Four waves a SIMD
+// in FP32 (128 registers) spill and are 11% slower.  Waves in two roles, one
+// predicting plane k + 1 while another solves plane k, pass every face state
+// through LDS and were 12% slower (14% on the hierarchy).
 //
 // Face fluxes that the coarse/fine registers read afterwards are still
 // stored: a per-element mask marks them (bit d for the face normal to d) and
@@ -67,20 +81,16 @@ __device__ __forceinline__ bool owns(int t, int tdim, int c, int clo, int chi) {
   return (t >= 1 && t <= tdim - 2) || (t == 0 && c == clo) || (t == tdim - 1 && c == chi);
 }
 
-template <class T, int NDIM, bool PERSIST>
-__global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grids, const FluxItem* __restrict__ items,
-                                               int nitems, StatePair<T> S, uint32_t parity,
-                                               DevFlux<T> F, const uint8_t* __restrict__ fmask,
-                                               const double* __restrict__ dt0p, Phys ph, ErrBlock* err, WorkQueue* q,
-                                               bool xcd, int claim) {
+// 2-D: the tile is one plane.
+template <class T, bool PERSIST>
+__global__ __launch_bounds__(256) void k_fused2(const GridDesc* __restrict__ grids, const FluxItem* __restrict__ items,
+                                                int nitems, StatePair<T> S, uint32_t parity, DevFlux<T> F,
+                                                const uint8_t* __restrict__ fmask, const double* __restrict__ dt0p,
+                                                Phys ph, ErrBlock* err, WorkQueue* q, bool xcd, int claim) {
+  constexpr int NDIM = 2;
   __shared__ T sW[8][kMaxPlane + 1];  // (the last entry takes the writes of lanes outside the tile)
-  __shared__ T sX[7][256];
-  __shared__ T sY[7][256];
-  __shared__ T sH[2][10][256];  // hydro components 0..4 of the x- (0..4) and y-face (5..9) fluxes, by plane parity
-  __shared__ T sB[4][256];      // EMF inputs of this plane: F_x c5, F_y c6, F_z c5, F_z c6 (2-D: F_x c6, F_y c5)
-  __shared__ T sEz[2][256];     // E_z at each lane's (x, y) low corner, by plane parity
-  __shared__ T sX6[2][256];     // 3-D: F_x c6 and F_y c5 of each lane, by plane parity (the inputs of
-  __shared__ T sY5[2][256];     // the neighbours' E_x, E_y, formed again where the z-faces need them)
+  // the plane's high face states (x in 0..6, y in 7..13), then its fluxes
+  __shared__ T sF[14][256];
   __shared__ int s_claim[2], s_c;
   if (threadIdx.x == 0) s_c = 0;
 
@@ -105,7 +115,7 @@ __global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grid
     const int chx = G.n[0] + gv - 1, chy = G.n[1] + gv - 1;
     const int wlo = -gv, whix = G.n[0] + gv, whiy = G.n[1] + gv;
     const int ul = -gv + 2;
-    const int uhx = G.n[0] + gv - 2, uhy = G.n[1] + gv - 2, uhz = NDIM == 3 ? G.n[2] + gv - 2 : 1;
+    const int uhx = G.n[0] + gv - 2, uhy = G.n[1] + gv - 2;
     const int x0 = item.x0, y0 = item.y0;
     const int tw = item.tw, th = 256 / tw, kW = tw + 2;
     const int tx = tid % tw, ty = tid / tw;
@@ -127,12 +137,174 @@ __global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grid
     const unsigned smask = sxy ? (xf ? 1u : 0u) | (yf ? 2u : 0u) | (act ? 4u : 0u) : 0u;
     // Every lane runs the whole plane: lanes without a cell of the launch
     // load a clamped cell of the box and read clamped LDS entries, and what
-    // they form is used by nobody (a lone wave of a SIMD issues one
-    // instruction every four cycles, scalar or vector, so execution masks
-    // around each piece cost more than the idle lanes).
+    // they form is used by nobody (masks around each piece cost scalar
+    // instructions, which share the waves' issue slots).
     const int lx = min(max(cx, wlo), whix - 1), ly = min(max(cy, wlo), whiy - 1);
     const int tl = max(tid - 1, 0), td = max(tid - tw, 0);        // low x and y neighbours
     const int tr = min(tid + 1, 255), tu = min(tid + tw, 255);    // high ones
+    const int tdr = max(tid - tw + 1, 0), tul = min(tid + tw - 1, 255);  // low y of the high x, and the reverse
+
+    double rl = 1.0;
+    for (int l = 0; l < G.level; ++l) rl *= (double)ph.ratio;
+    const T dt = T(dt0p[0] / rl);
+    const T cdx = dt * T(rl / ph.dx0[0]), cdy = dt * T(rl / ph.dx0[1]);
+
+    const int eo = live ? (ty + 1) * kW + tx + 1 : kW + 1;  // LDS plane entry read around
+    const int ew = live ? eo : kMaxPlane;                   // and written
+    const int nring = 2 * (tw + th);
+    int rex = 0, rey = 0;
+    if (tid < nring) ring_entry(tid, tw, th, rex, rey);
+    const int rcx = x0 - 2 + rex, rcy = y0 - 2 + rey;
+    const bool ring = tid < nring;
+    const bool rok = ring && rcx >= wlo && rcx < whix && rcy >= wlo && rcy < whiy;
+
+    T w[8], fb[3][2];
+    {
+      T wring[8];
+      load_prim_faces_b<T, NDIM>(U, bx(lx, ly, 0), bx.sy, bx.sz, gm1, w, fb);
+      if (rok) load_prim_b<T, NDIM>(U, bx(rcx, rcy, 0), bx.sy, bx.sz, gm1, wring);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        sW[c][ew] = w[c];
+        if (ring) sW[c][rey * kW + rex] = rok ? wring[c] : T(1);
+      }
+    }
+    const unsigned mk = (fmask ? fmask[ix(lx, ly, 0)] : 0u) & smask;
+    const auto eb = bx(lx, ly, 0);
+    T uo[8];  // the old values of everything the tile updates
+#pragma unroll
+    for (int s = 0; s < 8; ++s) uo[s] = ldb(U.f[s], eb);
+    __syncthreads();
+    T ml[2][7];
+    {
+      T wxm[8], wxp[8], wym[8], wyp[8], sl[3][8], du[8];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        wxm[c] = sW[c][eo - 1];
+        wxp[c] = sW[c][eo + 1];
+        wym[c] = sW[c][eo - kW];
+        wyp[c] = sW[c][eo + kW];
+      }
+      const T hcdt[3] = {T(0.5) * cdx, T(0.5) * cdy, T(0)};
+      hancock_slopes<T, NDIM>(w, wxm, wxp, wym, wyp, w, w, fb, hcdt, gm1_inv, sl, du);
+      const bool ok = hancock_states<T, NDIM>(w, sl, du, fb, gm1, gm1_inv,
+                                              [&](int d, const T (&lo)[7], const T (&hi)[7]) {
+#pragma unroll
+                                                for (int c = 0; c < 7; ++c) {
+                                                  ml[d][c] = lo[c];
+                                                  sF[7 * d + c][tid] = hi[c];
+                                                }
+                                              });
+      if (act && (!ok || w[0] <= T(0) || w[4] <= T(0))) flag_bad(err, ix(cx, cy, 0));
+    }
+    __syncthreads();
+    T fx[7], fy[7], l[7];
+#pragma unroll
+    for (int c = 0; c < 7; ++c) l[c] = sF[c][tl];
+    hlld7(l, ml[0], fb[0][0], gam, gm1_inv, fx);
+#pragma unroll
+    for (int c = 0; c < 7; ++c) l[c] = sF[7 + c][td];
+    hlld7(l, ml[1], fb[1][0], gam, gm1_inv, fy);
+    __syncthreads();  // the face states have been read: the fluxes take their place
+#pragma unroll
+    for (int c = 0; c < 7; ++c) {
+      sF[c][tid] = fx[c];
+      sF[7 + c][tid] = fy[c];
+    }
+    if (mk & 1u) st_flux7(F, 0, eb, fx);
+    if (mk & 2u) st_flux7(F, 1, eb, fy);
+    __syncthreads();
+    // E_z at this lane's (cx - 1/2, cy - 1/2) corner and at its high x and
+    // high y neighbours', from the inputs those lanes form theirs from
+    const T ez0 = emf_mean(sF[5][td], fx[5], sF[13][tl], fy[6]);
+    const T ezx = emf_mean(sF[5][tdr], sF[5][tr], fy[6], sF[13][tr]);
+    const T ezy = emf_mean(fx[5], sF[5][tu], sF[13][tul], sF[13][tu]);
+    if (ucell) {
+#pragma unroll
+      for (int s = 0; s < 5; ++s) {
+        const int qx = hydro_comp(s, 0), qy = hydro_comp(s, 1);
+        stb(V.f[s], eb, uo[s] - flux_delta2<T>(cdx, sF[qx][tr], fx[qx], cdy, sF[7 + qy][tu], fy[qy]));
+      }
+      stb(V.f[7], eb, uo[7] - flux_delta2<T>(cdx, sF[6][tr], fx[6], cdy, sF[12][tu], fy[5]));
+    }
+    if (ubx) stb(V.f[5], eb, uo[5] - face_delta2(cdy, ezy, ez0));
+    if (uby) stb(V.f[6], eb, uo[6] + face_delta2(cdx, ezx, ez0));
+    __syncthreads();
+  }
+  retire<PERSIST>(q);
+}
+
+// Values that are formed here and not sunk past a barrier to where they are
+// used (their inputs would be held in registers instead, which are scarcer).
+template <class T, int N> __device__ __forceinline__ void form_now(T (&a)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(a[i]));
+}
+
+// 3-D: the tile marches along z.  Two blocks share a CU.
+template <class T, bool PERSIST>
+__global__ __launch_bounds__(256, (sizeof(T) == 8 ? 2 : 3)) void k_fused3(
+    const GridDesc* __restrict__ grids, const FluxItem* __restrict__ items, int nitems, StatePair<T> S,
+    uint32_t parity, DevFlux<T> F, const uint8_t* __restrict__ fmask, const double* __restrict__ dt0p, Phys ph,
+    ErrBlock* err, WorkQueue* q, bool xcd, int claim) {
+  constexpr int NDIM = 3;
+  __shared__ T sW[8][kMaxPlane + 1];  // W of a plane (the last entry takes the writes of lanes outside the tile)
+  // one plane's high face states (x in 0..6, y in 7..13), then its fluxes:
+  // F_x in 0..6, F_y in 7..13, the two EMF components of F_z in 14, 15
+  __shared__ T sF[16][256];
+  __shared__ T sD[8][256];  // W of the lane's cell minus the plane below
+  __shared__ int s_claim[2], s_c;
+  if (threadIdx.x == 0) s_c = 0;
+
+  const int tid = threadIdx.x;
+  const T gam = T(ph.gamma);
+  const T gm1 = gam - T(1);
+  const T gm1_inv = drcp(gm1);
+
+  ItemRange rng = first_claim<PERSIST>(nitems, claim, xcd);
+  for (;;) {
+    const int it = next_item<PERSIST>(rng, nitems, claim, q, s_claim, &s_c, xcd);
+    if (it < 0) break;
+    const FluxItem item = items[it];
+    const GridDesc G = grids[item.grid];
+    const bool odd = (parity >> G.level) & 1u;
+    const DevState<T> U = S.s[odd ? 1 : 0];
+    const DevState<T> V = S.s[odd ? 0 : 1];
+    const Idx<NDIM> ix(G);
+    const IdxB<NDIM, T> bx(G);
+    const int gv = item.gv;
+    const int cl = -gv + 1;
+    const int chx = G.n[0] + gv - 1, chy = G.n[1] + gv - 1;
+    const int wlo = -gv, whix = G.n[0] + gv, whiy = G.n[1] + gv;
+    const int ul = -gv + 2;
+    const int uhx = G.n[0] + gv - 2, uhy = G.n[1] + gv - 2;
+    const int x0 = item.x0, y0 = item.y0;
+    const int tw = item.tw, th = 256 / tw, kW = tw + 2;
+    const int tx = tid % tw, ty = tid / tw;
+    const bool live = ty < th;
+    const int cx = x0 - 1 + tx, cy = y0 - 1 + ty;
+    const bool act = live && cx >= cl && cx < chx && cy >= cl && cy < chy;
+    const bool xf = act && tx >= 1 && cx > cl;  // its cell's low x-face is a face of the launch
+    const bool yf = act && ty >= 1 && cy > cl;  // low y-face
+    // update ownership: cells and z-faces at interior lanes; x- and y-faces
+    // also the update region's last face (uh), wherever it falls
+    const bool ucol = tx >= 1 && tx <= tw - 2 && cx >= ul && cx < uhx;
+    const bool urow = ty >= 1 && ty <= th - 2 && cy >= ul && cy < uhy;
+    const bool ucell = live && ucol && urow;
+    const bool ubx = live && urow && (ucol || (tx >= 1 && cx == uhx));
+    const bool uby = live && ucol && (urow || (ty >= 1 && cy == uhy));
+    // flux stores for the registers: one owning lane per computed face (mask
+    // bits of the faces this lane stores)
+    const bool sxy = owns(tx, tw, cx, cl, chx - 1) && owns(ty, th, cy, cl, chy - 1);
+    const unsigned smask = sxy ? (xf ? 1u : 0u) | (yf ? 2u : 0u) | (act ? 4u : 0u) : 0u;
+    // Every lane runs the whole plane: lanes without a cell of the launch
+    // load a clamped cell of the box and read clamped LDS entries, and what
+    // they form is used by nobody (masks around each piece cost scalar
+    // instructions, which share the waves' issue slots).
+    const int lx = min(max(cx, wlo), whix - 1), ly = min(max(cy, wlo), whiy - 1);
+    const int tl = max(tid - 1, 0), td = max(tid - tw, 0);        // low x and y neighbours
+    const int tr = min(tid + 1, 255), tu = min(tid + tw, 255);    // high ones
+    const int tdr = max(tid - tw + 1, 0), tul = min(tid + tw - 1, 255);  // low y of the high x, and the reverse
 
     double rl = 1.0;
     for (int l = 0; l < G.level; ++l) rl *= (double)ph.ratio;
@@ -151,222 +323,190 @@ __global__ __launch_bounds__(256) void k_fused(const GridDesc* __restrict__ grid
 
     // planes: update planes [z0, z1) (cells below uhz; z-faces up to uhz);
     // predicted states from z0 - 1 to the last plane whose fluxes they need
-    const int z0 = NDIM == 3 ? item.z0 : 0, z1 = NDIM == 3 ? item.z1 : 1;
-    const int kstart = NDIM == 3 ? z0 - 1 : 0;
-    const int kend = NDIM == 3 ? min(z1, uhz) : 0;  // inclusive
+    const int uhz = G.n[2] + gv - 2;
+    const int z0 = item.z0, z1 = item.z1;
+    const int kstart = z0 - 1;
+    const int kend = min(z1, uhz);  // inclusive
 
-    T dzm[8], wcur[8], wnext[8], wring[8];  // dzm: wcur minus the plane below
-    T fbcur[3][2], fbnext[3][2];
-    T zcarry[7];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) { dzm[c] = T(0); wnext[c] = T(1); wring[c] = T(1); }
-#pragma unroll
-    for (int c = 0; c < 7; ++c) zcarry[c] = T(1);
-    // carried from the previous plane: z-flux hydro components at k - 1/2,
-    // E_x and E_y at the low z-edges, F_y c5 and F_x c6 of the plane
-    T fzp[5] = {T(0), T(0), T(0), T(0), T(0)};
-    T exp_ = T(0), eyp_ = T(0), fy5p = T(0), fx6p = T(0);
+    const bool rwave = __builtin_amdgcn_readfirstlane(tid) < nring;  // (waves without ring lanes skip the ring)
+    const int rx = rok ? rcx : lx, ry = rok ? rcy : ly, rw = rok ? rey * kW + rex : kMaxPlane;
 
+    T wnext[8], fb[3][2], zlo[7];  // W of plane k + 1; face fields of plane k; high z states of plane k - 1
 #pragma unroll
-    for (int d = 0; d < 3; ++d) fbcur[d][0] = fbcur[d][1] = fbnext[d][0] = fbnext[d][1] = T(0);
-    if (NDIM == 3) {
+    for (int c = 0; c < 7; ++c) zlo[c] = T(1);
+    // carried from the plane below: the updates of its cells and x- and
+    // y-faces without the terms of the z-faces above them, and the EMF inputs
+    // F_y c5, F_x c6 of the lane, of its high x (F_x c6) and high y (F_y c5)
+    T up[7] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
+    T fy5p = T(0), fx6p = T(0), fx6r = T(0), fy5u = T(0);
+    {
       // the item's first planes: every load issued before any conversion
-      T r0[5], r1[5], r2[5], rr[5], f0[3][2], fr[3][2], wprev[8];
+      T r0[5], r1[5], r2[5], rr[5], f0[3][2], f2[3][2], fr[3][2], w0[8], w1[8], wring[8];
       load_raw3<T>(U, bx(lx, ly, kstart - 1), bx.sy, bx.sz, r0, f0);
-      load_raw3<T>(U, bx(lx, ly, kstart), bx.sy, bx.sz, r1, fbcur);
-      load_raw3<T>(U, bx(lx, ly, kstart + 1), bx.sy, bx.sz, r2, fbnext);
-      if (rok) load_raw3<T>(U, bx(rcx, rcy, kstart), bx.sy, bx.sz, rr, fr);
-      raw3_to_prim<T>(r0, f0, gm1, wprev);
-      raw3_to_prim<T>(r1, fbcur, gm1, wcur);
-      raw3_to_prim<T>(r2, fbnext, gm1, wnext);
-      if (rok) raw3_to_prim<T>(rr, fr, gm1, wring);
+      load_raw3<T>(U, bx(lx, ly, kstart), bx.sy, bx.sz, r1, fb);
+      load_raw3<T>(U, bx(lx, ly, kstart + 1), bx.sy, bx.sz, r2, f2);
+      load_raw3<T>(U, bx(rx, ry, kstart), bx.sy, bx.sz, rr, fr);
+      raw3_to_prim<T>(r0, f0, gm1, w0);
+      raw3_to_prim<T>(r1, fb, gm1, w1);
+      raw3_to_prim<T>(r2, f2, gm1, wnext);
+      raw3_to_prim<T>(rr, fr, gm1, wring);
 #pragma unroll
-      for (int c = 0; c < 8; ++c) dzm[c] = wcur[c] - wprev[c];
-    } else {
-      load_prim_faces_b<T, NDIM>(U, bx(lx, ly, kstart), bx.sy, bx.sz, gm1, wcur, fbcur);
-      if (rok) load_prim_b<T, NDIM>(U, bx(rcx, rcy, kstart), bx.sy, bx.sz, gm1, wring);
+      for (int c = 0; c < 8; ++c) {
+        sD[c][tid] = w1[c] - w0[c];
+        if (ring && !rok) sW[c][rey * kW + rex] = T(1);
+        sW[c][rw] = wring[c];
+        sW[c][ew] = w1[c];
+      }
     }
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      sW[c][ew] = wcur[c];
-      if (ring) sW[c][rey * kW + rex] = wring[c];
-    }
+    unsigned mk = (fmask ? ldb(fmask, bx(lx, ly, kstart) / (unsigned)sizeof(T)) : 0u) & smask;
     __syncthreads();
-
-    unsigned mknext = fmask ? fmask[ix(lx, ly, kstart)] : 0u;
     for (int k = kstart; k <= kend; ++k) {
-      const int pb = k & 1;
-      // this plane's face mask was loaded an iteration ago; the next one's
-      // load is in flight through this iteration
-      const unsigned mk = mknext & smask;
-      if (fmask && k + 1 <= kend) mknext = fmask[ix(lx, ly, k + 1)];
-      T rnext[5], rfb[3][2], rring[5], rrfb[3][2];
-      const bool rn = NDIM == 3 && rok && k + 1 <= kend;
-      if (NDIM == 3) {
-        // (the last iterations load the last plane again: no branch)
-        load_raw3<T>(U, bx(lx, ly, min(k + 2, kend + 1)), bx.sy, bx.sz, rnext, rfb);
-        if (rn) load_raw3<T>(U, bx(rcx, rcy, k + 1), bx.sy, bx.sz, rring, rrfb);
-      }
-      Pred<T, NDIM> pr;
-      T dzp[8];
-#pragma unroll
-      for (int c = 0; c < 8; ++c) dzp[c] = wnext[c] - wcur[c];
+      T ml[3][7], zhi[7];  // low face states; the high z state
       {
-        T wxm[8], wxp[8], wym[8], wyp[8];
+        T w[8], sl[3][8], du[8];
+        {
+          T wxm[8], wxp[8], wym[8], wyp[8], dzm[8], dzp[8];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          wxm[c] = sW[c][eo - 1];
-          wxp[c] = sW[c][eo + 1];
-          wym[c] = sW[c][eo - kW];
-          wyp[c] = sW[c][eo + kW];
-        }
-        const T hcdt[3] = {T(0.5) * cdx, T(0.5) * cdy, T(0.5) * cdz};
-        const bool ok = predict<T, NDIM>(wcur, wxm, wxp, wym, wyp, dzm, dzp, fbcur, hcdt, gm1, gm1_inv, pr);
-        if (act && (!ok || wcur[0] <= T(0) || wcur[4] <= T(0))) flag_bad(err, ix(cx, cy, k));
+          for (int c = 0; c < 8; ++c) {
+            w[c] = sW[c][eo];
+            dzm[c] = sD[c][tid];
+            dzp[c] = wnext[c] - w[c];
+            sD[c][tid] = dzp[c];
+            wxm[c] = sW[c][eo - 1];
+            wxp[c] = sW[c][eo + 1];
+            wym[c] = sW[c][eo - kW];
+            wyp[c] = sW[c][eo + kW];
+          }
+          const T hcdt[3] = {T(0.5) * cdx, T(0.5) * cdy, T(0.5) * cdz};
+          hancock_slopes<T, NDIM>(w, wxm, wxp, wym, wyp, dzm, dzp, fb, hcdt, gm1_inv, sl, du);
 #pragma unroll
-        for (int c = 0; c < 7; ++c) {
-          sX[c][tid] = pr.p[0][c];
-          sY[c][tid] = pr.p[1][c];
+          for (int d = 0; d < 3; ++d) form_now(sl[d]);
+          form_now(du);
         }
+        __syncthreads();  // the plane below's fluxes have been read: the face states take their place
+        const bool ok = hancock_states<T, NDIM>(w, sl, du, fb, gm1, gm1_inv,
+                                                [&](int d, const T (&lo)[7], const T (&hi)[7]) {
+#pragma unroll
+                                                  for (int c = 0; c < 7; ++c) {
+                                                    ml[d][c] = lo[c];
+                                                    if (d == 2) zhi[c] = hi[c];
+                                                    else sF[7 * d + c][tid] = hi[c];
+                                                  }
+                                                });
+        if (act && (!ok || w[0] <= T(0) || w[4] <= T(0))) flag_bad(err, ix(cx, cy, k));
       }
-      __syncthreads();
-      // this plane's W has been read: the next plane's goes into LDS while
-      // the Riemann problems run
-      T bn[3] = {fbcur[0][0], fbcur[1][0], fbcur[2][0]};
-      if (NDIM == 3) {
-        if (rn) raw3_to_prim<T>(rring, rrfb, gm1, wring);
+      const T bn[3] = {fb[0][0], fb[1][0], fb[2][0]};
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          sW[c][ew] = wnext[c];
-          if (ring) sW[c][rey * kW + rex] = wring[c];
-          dzm[c] = dzp[c];
-          wcur[c] = wnext[c];
-        }
+      for (int d = 0; d < 3; ++d) form_now(ml[d]);
+      form_now(zhi);
+      __syncthreads();  // this plane's W has been read, the face states are in place
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          fbcur[d][0] = fbnext[d][0];
-          fbcur[d][1] = fbnext[d][1];
-        }
-        raw3_to_prim<T>(rnext, rfb, gm1, wnext);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          fbnext[d][0] = rfb[d][0];
-          fbnext[d][1] = rfb[d][1];
-        }
-      }
-      const bool zf = NDIM == 3 && k >= z0;
-      const auto eb = bx(lx, ly, k);
+      for (int c = 0; c < 8; ++c) sW[c][ew] = wnext[c];
+      const auto eb = bx(lx, ly, k), ep = bx(lx, ly, k - 1), en = bx(lx, ly, min(k + 1, kend + 1));
+      const bool own = (k >= z0 && k < z1) || (k == kstart && z0 == ul);
       T fx[7], fy[7], fz[7];
+      {
+        T l7[7];
+#pragma unroll
+        for (int c = 0; c < 7; ++c) l7[c] = sF[c][tl];
+        hlld7(l7, ml[0], bn[0], gam, gm1_inv, fx);
+      }
+      {
+        T l7[7];
+#pragma unroll
+        for (int c = 0; c < 7; ++c) l7[c] = sF[7 + c][td];
+        hlld7(l7, ml[1], bn[1], gam, gm1_inv, fy);
+      }
+      // the loads behind this plane's fluxes: the ring of plane k + 1, the
+      // raw fields of plane k + 2, the face fields of plane k + 1 and the old
+      // values of what the update writes (converted and used before its
+      // stores: a wait for loads would wait for stores issued after them)
+      T rring[5], rrfb[3][2], rnext[5], rfb[3][2], uo[7];
+#pragma unroll
+      for (int c = 0; c < 5; ++c) rring[c] = T(1);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) rrfb[d][0] = rrfb[d][1] = T(0);
+      if (rwave) load_raw3<T>(U, bx(rx, ry, min(k + 1, kend)), bx.sy, bx.sz, rring, rrfb);
 #pragma unroll
       for (int c = 0; c < 7; ++c) fz[c] = T(0);
-      {
-        T l[7];
+      if (k >= z0) hlld7(zlo, ml[2], bn[2], gam, gm1_inv, fz);
 #pragma unroll
-        for (int c = 0; c < 7; ++c) l[c] = sX[c][tl];
-        hlld7(l, pr.m[0], bn[0], gam, gm1_inv, fx);
-      }
-      {
-        T l[7];
+      for (int c = 0; c < 7; ++c) zlo[c] = zhi[c];
+      load_raw3<T>(U, bx(lx, ly, min(k + 2, kend + 1)), bx.sy, bx.sz, rnext, rfb);
 #pragma unroll
-        for (int c = 0; c < 7; ++c) l[c] = sY[c][td];
-        hlld7(l, pr.m[1], bn[1], gam, gm1_inv, fy);
-      }
-      if (zf) hlld7(zcarry, pr.m[2], bn[2], gam, gm1_inv, fz);
-      if (mk != 0u) {
-        const bool own = NDIM == 2 || (k >= z0 && k < z1);
-        if ((mk & 1u) && (own || (k == kstart && z0 == ul))) st_flux7(F, 0, eb, fx);
-        if ((mk & 2u) && (own || (k == kstart && z0 == ul))) st_flux7(F, 1, eb, fy);
-        if (NDIM == 3 && (mk & 4u) && own) st_flux7(F, 2, eb, fz);
-      }
-      if (NDIM == 3) {
+      for (int s = 0; s < 7; ++s) uo[s] = ldb(U.f[s], ep);
+      fb[0][0] = ldb(U.f[5], en);
+      fb[0][1] = ldb(U.f[5], en, (int)sizeof(T));
+      fb[1][0] = ldb(U.f[6], en);
+      fb[1][1] = ldb(U.f[6], en + bx.sy);
+      fb[2][0] = ldb(U.f[7], en);
+      const unsigned mkn = fmask ? ldb(fmask, en / (unsigned)sizeof(T)) : 0u;
+      __syncthreads();  // the face states have been read: the fluxes take their place
 #pragma unroll
-        for (int c = 0; c < 7; ++c) zcarry[c] = pr.p[2][c];
+      for (int c = 0; c < 7; ++c) {
+        sF[c][tid] = fx[c];
+        sF[7 + c][tid] = fy[c];
       }
+      sF[14][tid] = fz[5];
+      sF[15][tid] = fz[6];
+      if (rwave) {
+        T wring[8];
+        raw3_to_prim<T>(rring, rrfb, gm1, wring);
 #pragma unroll
-      for (int c = 0; c < 5; ++c) {
-        sH[pb][c][tid] = fx[c];
-        sH[pb][5 + c][tid] = fy[c];
-      }
-      sB[0][tid] = fx[5];
-      sB[1][tid] = fy[6];
-      if (NDIM == 3) {
-        sB[2][tid] = fz[5];
-        sB[3][tid] = fz[6];
-        sX6[pb][tid] = fx[6];
-        sY5[pb][tid] = fy[5];
-      } else {
-        sB[2][tid] = fx[6];
-        sB[3][tid] = fy[5];
+        for (int c = 0; c < 8; ++c) sW[c][rw] = wring[c];
       }
       __syncthreads();
-      // edge EMFs: E_z at (cx - 1/2, cy - 1/2) of plane k; E_x at
-      // (cx, cy - 1/2) and E_y at (cx - 1/2, cy), both at z = k - 1/2
-      sEz[pb][tid] = emf_mean(sB[0][td], fx[5], sB[1][tl], fy[6]);
-      // 2-D: the faces read E_z of the neighbours' corners, formed above; in
-      // 3-D every input of this plane's update is in LDS already (E_z of the
-      // plane below, and the inputs of the neighbours' E_x, E_y)
-      if (NDIM == 2) __syncthreads();
-      if (NDIM == 3) {
-        const T ex = emf_mean(fy5p, fy[5], sB[3][td], fz[6]);
-        const T ey = emf_mean(sB[2][tl], fz[5], fx6p, fx[6]);
-        // the old values of everything this plane updates are loaded before
-        // any store, so their latencies overlap
-        const int kk = k - 1;
-        const bool zup = ucell && k >= z0 && k < z1;
-        const bool cup = kk >= z0 && kk < z1 && kk < uhz;
-        const auto ec = bx(lx, ly, kk);
-        T uo[8];
-        uo[7] = ldb(U.f[7], eb);
+      // edge EMFs: E_z at this lane's (cx - 1/2, cy - 1/2) corner of plane k
+      // and at its high x and high y neighbours'; E_x at (cx, cy - 1/2) and
+      // E_y at (cx - 1/2, cy) of z = k - 1/2 and those of the high y and high
+      // x neighbours, from the inputs those lanes form theirs from
+      const T fx5r = sF[5][tr], fx6n = sF[6][tr], fy6r = sF[13][tr];
+      const T fx5u = sF[5][tu], fy5n = sF[12][tu], fy6u = sF[13][tu];
+      const T ez0 = emf_mean(sF[5][td], fx[5], sF[13][tl], fy[6]);
+      const T ezx = emf_mean(sF[5][tdr], fx5r, fy[6], fy6r);
+      const T ezy = emf_mean(fx[5], fx5u, sF[13][tul], fy6u);
+      const T ex = emf_mean(fy5p, fy[5], sF[15][td], fz[6]);
+      const T ey = emf_mean(sF[14][tl], fz[5], fx6p, fx[6]);
+      const T ey1 = emf_mean(fz[5], sF[14][tr], fx6r, fx6n);
+      const T ex1 = emf_mean(fy5u, fy5n, fz[6], sF[15][tu]);
+      fy5p = fy[5];
+      fx6p = fx[6];
+      fx6r = fx6n;
+      fy5u = fy5n;
+      T un[8];
+      un[7] = bn[2] - curl_delta(cdx, ey1, ey, cdy, ex1, ex);
 #pragma unroll
-        for (int s = 0; s < 7; ++s) uo[s] = ldb(U.f[s], ec);
-        // z-faces at k - 1/2 (element of plane k): E_y of the next lane's and
-        // E_x of the next row's low z-edge, from the same inputs as those
-        // lanes form them
-        const int qb = kk & 1;
-        const T ey1 = emf_mean(sB[2][tid], sB[2][tr], sX6[qb][tr], sX6[pb][tr]);
-        const T ex1 = emf_mean(sY5[qb][tu], sY5[pb][tu], sB[3][tid], sB[3][tu]);
-        if (zup) stb(V.f[7], eb, uo[7] - curl_delta(cdx, ey1, ey, cdy, ex1, ex));
-        // cells and x-, y-faces of plane k - 1
-        if (cup) {
-          const T ez0 = sEz[qb][tid], ezy = sEz[qb][tu], ezx = sEz[qb][tr];
-          T un[5];
+      for (int s = 0; s < 5; ++s) {
+        const int qx = hydro_comp(s, 0), qy = hydro_comp(s, 1), qz = hydro_comp(s, 2);
+        un[s] = uo[s] - add_high(up[s], cdz, fz[qz]);
+        // plane k's, up to the z-faces above it
+        up[s] = flux_low<T>(cdx, sF[qx][tr], fx[qx], cdy, sF[7 + qy][tu], fy[qy], cdz, fz[qz]);
+      }
+      un[5] = uo[5] - add_high(up[5], -cdz, ey);
+      un[6] = uo[6] - add_high(up[6], cdz, ex);
+      up[5] = curl_low(cdy, ezy, ez0, cdz, ey);
+      up[6] = curl_low(-cdx, ezx, ez0, -cdz, ex);
+      fb[2][1] = rfb[2][0];
+      raw3_to_prim<T>(rnext, rfb, gm1, wnext);
+      form_now(wnext);
+      form_now(fb[0]);
+      form_now(fb[1]);
+      form_now(fb[2]);
+      if (mk != 0u) {
+        if ((mk & 1u) && own) st_flux7(F, 0, eb, fx);
+        if ((mk & 2u) && own) st_flux7(F, 1, eb, fy);
+        if ((mk & 4u) && k >= z0 && k < z1) st_flux7(F, 2, eb, fz);
+      }
+      mk = mkn & smask;
+      // z-faces at k - 1/2 (element of plane k)
+      if (ucell && k >= z0 && k < z1) stb(V.f[7], eb, un[7]);
+      // cells and x-, y-faces of plane k - 1
+      if (k - 1 >= z0 && k - 1 < z1 && k - 1 < uhz) {
+        if (ucell)
 #pragma unroll
-          for (int s = 0; s < 5; ++s) {
-            const int qx = hydro_comp(s, 0), qy = hydro_comp(s, 1), qz = hydro_comp(s, 2);
-            const T acc = flux_delta<T, 3>(cdx, sH[qb][qx][tr], sH[qb][qx][tid], cdy, sH[qb][5 + qy][tu],
-                                           sH[qb][5 + qy][tid], cdz, fz[qz], fzp[qz]);
-            un[s] = uo[s] - acc;
-          }
-          if (ucell)
-#pragma unroll
-            for (int s = 0; s < 5; ++s) stb(V.f[s], ec, un[s]);
-          if (ubx) stb(V.f[5], ec, uo[5] - curl_delta(cdy, ezy, ez0, cdz, ey, eyp_));
-          if (uby) stb(V.f[6], ec, uo[6] - curl_delta(cdz, ex, exp_, cdx, ezx, ez0));
-        }
-#pragma unroll
-        for (int c = 0; c < 5; ++c) fzp[c] = fz[c];
-        exp_ = ex;
-        eyp_ = ey;
-        fy5p = fy[5];
-        fx6p = fx[6];
-      } else {
-        // 2-D: the single plane's cells (B_z cell-centred) and faces
-        T uo[8];
-#pragma unroll
-        for (int s = 0; s < 8; ++s) uo[s] = ldb(U.f[s], eb);
-        if (ucell) {
-#pragma unroll
-          for (int s = 0; s < 5; ++s) {
-            const int qx = hydro_comp(s, 0), qy = hydro_comp(s, 1);
-            const T acc = flux_delta<T, 2>(cdx, sH[0][qx][tr], sH[0][qx][tid], cdy, sH[0][5 + qy][tu],
-                                           sH[0][5 + qy][tid], T(0), T(0), T(0));
-            stb(V.f[s], eb, uo[s] - acc);
-          }
-          const T acc = flux_delta<T, 2>(cdx, sB[2][tr], sB[2][tid], cdy, sB[3][tu], sB[3][tid], T(0), T(0), T(0));
-          stb(V.f[7], eb, uo[7] - acc);
-        }
-        if (ubx) stb(V.f[5], eb, uo[5] - face_delta2(cdy, sEz[0][tu], sEz[0][tid]));
-        if (uby) stb(V.f[6], eb, uo[6] + face_delta2(cdx, sEz[0][tr], sEz[0][tid]));
+          for (int s = 0; s < 5; ++s) stb(V.f[s], ep, un[s]);
+        if (ubx) stb(V.f[5], ep, un[5]);
+        if (uby) stb(V.f[6], ep, un[6]);
       }
     }
     __syncthreads();
@@ -382,19 +522,18 @@ void launch_fused(int ndim, const GridDesc* grids, const FluxItem* items, int ni
                   WorkQueue* q, int pblocks, bool xcd, int claim, hipStream_t s) {
   if (nitems <= 0) return;
   const bool per = pblocks > 0 && q != nullptr;
-  const dim3 grid(per ? std::min(pblocks, nitems) : claim_blocks(nitems, claim, xcd)), block(256);
+  const dim3 grid(per ? std::min(pblocks, nitems) : claim_blocks(nitems, claim, xcd));
   StatePair<T> SP;
   SP.s[0] = S0;
   SP.s[1] = S1;
-#define AMR_FUSED_LAUNCH(ND, P) \
-  hipLaunchKernelGGL((k_fused<T, ND, P>), grid, block, 0, s, grids, items, nitems, SP, parity, F, fmask, dt0, ph, err, q, \
-                     xcd, claim)
+#define AMR_FUSED_LAUNCH(K, THREADS) \
+  hipLaunchKernelGGL((K), grid, dim3(THREADS), 0, s, grids, items, nitems, SP, parity, F, fmask, dt0, ph, err, q, xcd, claim)
   if (ndim == 3) {
-    if (per) AMR_FUSED_LAUNCH(3, true);
-    else AMR_FUSED_LAUNCH(3, false);
+    if (per) AMR_FUSED_LAUNCH((k_fused3<T, true>), 256);
+    else AMR_FUSED_LAUNCH((k_fused3<T, false>), 256);
   } else {
-    if (per) AMR_FUSED_LAUNCH(2, true);
-    else AMR_FUSED_LAUNCH(2, false);
+    if (per) AMR_FUSED_LAUNCH((k_fused2<T, true>), 256);
+    else AMR_FUSED_LAUNCH((k_fused2<T, false>), 256);
   }
 #undef AMR_FUSED_LAUNCH
 }
@@ -402,9 +541,9 @@ void launch_fused(int ndim, const GridDesc* grids, const FluxItem* items, int ni
 template <class T> int fused_occupancy(int ndim) {
   int a = 0;
   if (ndim == 3)
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, k_fused<T, 3, true>, 256, 0);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, k_fused3<T, true>, 256, 0);
   else
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, k_fused<T, 2, true>, 256, 0);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, k_fused2<T, true>, 256, 0);
   return a > 0 ? a : 1;
 }
 

@@ -241,13 +241,13 @@ template <class T> __host__ __device__ __forceinline__ T fast_magnetosonic(T r, 
 // x/t = 0 is the first true test of S_L > 0, S*_L >= 0, S_M >= 0, S*_R >= 0,
 // S_R >= 0 (else the right state).  The star states satisfy the jump
 // conditions with the total pressure and normal velocity they share, so the
-// flux of every region is the physical flux of its state, evaluated once:
-// the inner (double-star) state of the chosen side, which subsonic and
-// sub-Alfvenic flow is in, or under a branch that few waves take the star or
-// the outer state.  Against forming every state and the jumps
-// F + S (U* - U) + S* (U** - U*) with selects between both sides this is
-// about 240 instead of 430 vector instructions in double (a select of a
-// double is two), and the kernels here are bound by their issue.
+// flux of every region is the physical flux of its state, evaluated once: the
+// inner (double-star) or star state of the chosen side by selects (waves hold
+// lanes of both), the outer state under a branch that subsonic flow skips.
+// Against forming every state's jump F + S (U* - U) + S* (U** - U*) with
+// selects between both sides this is about 260 instead of 430 vector
+// instructions in double (a select of a double is two), and the kernels here
+// are bound by their issue.
 template <class T>
 __host__ __device__ __forceinline__ void riemann_hlld(const T (&ql)[8], const T (&qr)[8], T bn, T gam, T gm1_inv,
                                                       T (&f)[7]) {
@@ -338,39 +338,33 @@ __host__ __device__ __forceinline__ void riemann_hlld(const T (&ql)[8], const T 
   const T isum = drcp(sql + sqr);
   const T ssg = sql * sqr * sg;
   const bool left = sm >= T(0) || sl > T(0);
-  T vb = sm * bn;
-  T v = (sql * vsl + sqr * vsr + (bysr - bysl) * sg) * isum;
-  T w = (sql * wsl + sqr * wsr + (bzsr - bzsl) * sg) * isum;
-  T by = (sql * bysr + sqr * bysl + ssg * (vsr - vsl)) * isum;
-  T bz = (sql * bzsr + sqr * bzsl + ssg * (wsr - wsl)) * isum;
-  vb = vb + v * by + w * bz;
-  T u = sm, pt = pts;
-  T r = left ? rsl : rsr;
-  T e = left ? esl - sql * sg * (vbsl - vb) : esr + sqr * sg * (vbsr - vb);
-
+  const T vss = (sql * vsl + sqr * vsr + (bysr - bysl) * sg) * isum;
+  const T wss = (sql * wsl + sqr * wsr + (bzsr - bzsl) * sg) * isum;
+  const T byss = (sql * bysr + sqr * bysl + ssg * (vsr - vsl)) * isum;
+  const T bzss = (sql * bzsr + sqr * bzsl + ssg * (wsr - wsl)) * isum;
+  const T vbss = sm * bn + vss * byss + wss * bzss;
   // The inner state holds x/t = 0 unless a test before it does or the normal
   // field is degenerate (the inner states then equal the star states).
-  const bool inner = (left ? !(sl > T(0)) && !(ssl >= T(0)) : ssr >= T(0)) && !(T(0.5) * bn2 <= tiny);
-  if (!inner) {
-    v = left ? vsl : vsr;
-    w = left ? wsl : wsr;
-    by = left ? bysl : bysr;
-    bz = left ? bzsl : bzsr;
-    vb = left ? vbsl : vbsr;
-    e = left ? esl : esr;
-    // the outer state beyond the fast waves; where the inner states are
-    // degenerate and the star region is passed over, the star state stands
-    if (left ? sl > T(0) : !(ssr >= T(0)) && !(sr >= T(0))) {
-      r = left ? ql[0] : qr[0];
-      u = left ? ql[1] : qr[1];
-      v = left ? ql[2] : qr[2];
-      w = left ? ql[3] : qr[3];
-      by = left ? ql[6] : qr[6];
-      bz = left ? ql[7] : qr[7];
-      pt = left ? ptl : ptr;
-      vb = u * bn + v * by + w * bz;
-      e = (left ? ql[4] : qr[4]) * gm1_inv + T(0.5) * (r * (u * u + v * v + w * w) + (left ? b2l : b2r));
-    }
+  const bool inner = (left ? !(ssl >= T(0)) : ssr >= T(0)) && !(T(0.5) * bn2 <= tiny);
+  T r = left ? rsl : rsr, u = sm, pt = pts;
+  T vb = left ? vbsl : vbsr;
+  T e = left ? esl : esr;
+  e = inner ? e - (left ? sql : -sqr) * sg * (vb - vbss) : e;
+  vb = inner ? vbss : vb;
+  T v = inner ? vss : (left ? vsl : vsr);
+  T w = inner ? wss : (left ? wsl : wsr);
+  T by = inner ? byss : (left ? bysl : bysr);
+  T bz = inner ? bzss : (left ? bzsl : bzsr);
+  if (left ? sl > T(0) : !(ssr >= T(0)) && !(sr >= T(0))) {  // beyond the fast waves: the outer state
+    r = left ? ql[0] : qr[0];
+    u = left ? ql[1] : qr[1];
+    v = left ? ql[2] : qr[2];
+    w = left ? ql[3] : qr[3];
+    by = left ? ql[6] : qr[6];
+    bz = left ? ql[7] : qr[7];
+    pt = left ? ptl : ptr;
+    vb = u * bn + v * by + w * bz;
+    e = (left ? ql[4] : qr[4]) * gm1_inv + T(0.5) * (r * (u * u + v * v + w * w) + (left ? b2l : b2r));
   }
   f[0] = r * u;
   f[1] = f[0] * u + (pt - bn2);
