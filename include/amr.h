@@ -328,7 +328,8 @@ amr_status amr_load_primitive_adjoint(amr_hierarchy* h, int32_t grid, const doub
  * per tile) that launches the fewest tiles over the grid.  zchunk: at most
  * this many planes per work item of the flux or fused kernel along z (3D): a
  * tile column of D planes is cut into ceil(D / zchunk) chunks of near-equal
- * length.  launch_mode bit 0: persistent launches (a fixed
+ * length, and into more of them where the launch would have fewer items than
+ * the device has CUs.  launch_mode bit 0: persistent launches (a fixed
  * grid of resident blocks popping the launch's item list from a device
  * queue, one atomic per claim of items, in list order: finest level first,
  * then inside each eighth of the flux list its longest items (most

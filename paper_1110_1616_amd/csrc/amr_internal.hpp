@@ -46,6 +46,7 @@ struct UpdItem {
 
 constexpr int kMinTile = 4;   // tile widths the kernels accept
 constexpr int kMaxTile = 64;
+constexpr int kComputeUnits = 256;  // of the device (the work lists are cut for it, also on hosts without one)
 
 // Physics constants passed by value.
 struct Phys {

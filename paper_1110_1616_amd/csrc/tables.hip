@@ -73,7 +73,63 @@ void check_tile(int tw) {
   if ((tw + 2) * (256 / tw + 2) > 396) throw Error(AMR_EINVAL, "internal: tile plane exceeds the LDS plane");
 }
 
-void add_grid_items(amr_hierarchy* h, int gi, int gv, std::vector<FluxItem>& fl, std::vector<UpdItem>& ul) {
+// Planes per work item of a list, at most zmax.  A launch ends with its last
+// item, and an item runs its planes one after the other, so a list with fewer
+// items than the device has CUs is cut into the shortest items that still
+// have a CU each, though each recomputes two or three planes at its ends
+// (37 x 33 x 35 in FP32, 9 tiles: a step's flux kernel 68 us at 16 planes an
+// item, 17 us at one; a 24^3 three-level hierarchy's coarse step 394 ->
+// 235 us; 72^3, 25 tiles, 16 -> 8 planes: 172 -> 146 us).  Longer lists keep
+// zmax: their items share CUs and caches already, and cutting them cost the
+// 549-grid hierarchy 4% and the 6-level one 6%.  columns: (tiles, planes) a
+// grid.
+int pick_planes(const std::vector<std::pair<int, int>>& columns, int zmax, int zmin) {
+  int dmax = 0;
+  for (auto& c : columns) dmax = std::max(dmax, c.second);
+  auto items = [&](int z) {
+    int64_t n = 0;
+    for (auto& c : columns) n += (int64_t)c.first * ((c.second + z - 1) / z);
+    return n;
+  };
+  int best = zmax;
+  for (int n = 1; n <= dmax; ++n) {
+    const int z = (dmax + n - 1) / n;
+    if (z >= best) continue;
+    if (z < zmin || items(z) > kComputeUnits) break;
+    best = z;
+  }
+  return best;
+}
+
+// Planes per item of a list's flux and fused items.
+struct ListPlanes {
+  int flux, fused;
+};
+
+ListPlanes list_planes(const amr_hierarchy* h, const std::vector<std::pair<int, int>>& grid_bands) {
+  ListPlanes r{h->zchunk, h->zchunk};
+  if (h->ndim != 3) return r;
+  std::vector<std::pair<int, int>> fc, xc;
+  for (auto& gb : grid_bands) {
+    const GridDesc& G = h->desc[gb.first];
+    const int m = 2 * gb.second;
+    auto tiles = [&](int W, int H, int ov) {
+      const int tw = pick_tile(W, H, ov, h->tile_policy), th = 256 / tw;
+      return ((W + tw - ov - 1) / (tw - ov)) * ((H + th - ov - 1) / (th - ov));
+    };
+    fc.push_back({tiles(G.n[0] + m - 2, G.n[1] + m - 2, 1), G.n[2] + m - 2});
+    xc.push_back({tiles(G.n[0] + m - 4, G.n[1] + m - 4, 2), G.n[2] + m - 3});
+  }
+  // lists of one grid of many (the per-grid path) keep some length: there are
+  // three for every grid
+  const int zmin = grid_bands.size() == 1 && h->grids.size() > 1 ? 4 : 1;
+  r.flux = pick_planes(fc, h->zchunk, zmin);
+  r.fused = pick_planes(xc, h->zchunk, zmin);
+  return r;
+}
+
+void add_grid_items(amr_hierarchy* h, int gi, int gv, const ListPlanes& planes, std::vector<FluxItem>& fl,
+                    std::vector<UpdItem>& ul) {
   const GridDesc& G = h->desc[gi];
   const int cl = -gv + 1;
   int ch[3], uh[3];
@@ -81,14 +137,14 @@ void add_grid_items(amr_hierarchy* h, int gi, int gv, std::vector<FluxItem>& fl,
     ch[d] = d < h->ndim ? G.n[d] + gv - 1 : 1;
     uh[d] = d < h->ndim ? G.n[d] + gv - 2 : 0;
   }
-  const int zc = h->zchunk;
   const int zlo = h->ndim == 3 ? cl : 0;
   const int ftw = pick_tile(ch[0] - cl, ch[1] - cl, 1, h->tile_policy), fth = 256 / ftw;
   check_tile(ftw);
-  // a column's planes in ceil(D / zc) chunks of near-equal length (each
+  const int zf = planes.flux, zx = planes.fused;
+  // a column's planes in ceil(D / z) chunks of near-equal length (each
   // chunk recomputes a plane or two at its ends, so a short remainder chunk
   // costs more per plane than an even split)
-  const int FD = ch[2] - zlo, fnz = h->ndim == 3 ? (FD + zc - 1) / zc : 1;
+  const int FD = ch[2] - zlo, fnz = h->ndim == 3 ? (FD + zf - 1) / zf : 1;
   for (int zi = 0; zi < fnz; ++zi)
     for (int y0 = cl; y0 < ch[1]; y0 += fth - 1)
       for (int x0 = cl; x0 < ch[0]; x0 += ftw - 1) {
@@ -129,7 +185,7 @@ void add_grid_items(amr_hierarchy* h, int gi, int gv, std::vector<FluxItem>& fl,
     check_tile(xtw);
     // the column's planes in near-equal chunks, as for the flux items
     const int xzhi = h->ndim == 3 ? uh[2] + 1 : 1;
-    const int D = xzhi - uzlo, nzc = h->ndim == 3 ? (D + zc - 1) / zc : 1;
+    const int D = xzhi - uzlo, nzc = h->ndim == 3 ? (D + zx - 1) / zx : 1;
     for (int zi = 0; zi < nzc; ++zi)
       for (int y0 = ul0; y0 < uh[1]; y0 += xth - 2)
         for (int x0 = ul0; x0 < uh[0]; x0 += xtw - 2) {
@@ -170,7 +226,8 @@ LaunchList make_list(amr_hierarchy* h, const std::vector<std::pair<int, int>>& g
   L.upd.off = (int)h->h_uitems.size();
   L.emf.off = (int)h->h_eitems.size();
   L.fused.off = (int)h->h_xitems.size();
-  for (auto& gb : grid_bands) add_grid_items(h, gb.first, gb.second, h->h_fitems, h->h_uitems);
+  const ListPlanes planes = list_planes(h, grid_bands);
+  for (auto& gb : grid_bands) add_grid_items(h, gb.first, gb.second, planes, h->h_fitems, h->h_uitems);
   L.emf.n = (int)h->h_eitems.size() - L.emf.off;
   L.fused.n = (int)h->h_xitems.size() - L.fused.off;
   L.flux.n = (int)h->h_fitems.size() - L.flux.off;
@@ -180,6 +237,14 @@ LaunchList make_list(amr_hierarchy* h, const std::vector<std::pair<int, int>>& g
   // With XCD chunking the order holds inside each eighth of the list (the
   // chunks of the launch), so items stay in their chunk, next to the tiles
   // they share halos with; without it, over the whole list.
+  // Without it, the runs of equal length of one grid's list are dealt out so
+  // that neighbouring tiles meet on one XCD all the same (blocks reach the
+  // XCDs round-robin by their index, and the first items of a launch go to
+  // them in that order): the positions of one XCD take a contiguous part of
+  // the run, and halos are read from its L2 instead of from memory (72^3,
+  // two-kernel upwinded step, 294 -> 282 us a pair; 128^3 fused 659 -> 645).
+  // A list of many grids keeps its order (dealt out, the 549-grid hierarchy's
+  // coarse steps are 1.8% slower).
   auto longest_first = [&](std::vector<FluxItem>& v, int off, int n) {
     const int parts = h->xcd_chunks ? 8 : 1;
     const int C = (n + parts - 1) / parts;
@@ -187,6 +252,22 @@ LaunchList make_list(amr_hierarchy* h, const std::vector<std::pair<int, int>>& g
       auto b = v.begin() + off + c * C;
       auto e = v.begin() + off + std::min(n, (c + 1) * C);
       std::stable_sort(b, e, [](const FluxItem& x, const FluxItem& y) { return x.z1 - x.z0 > y.z1 - y.z0; });
+    }
+    if (h->xcd_chunks || grid_bands.size() > 1) return;
+    std::vector<FluxItem> run;
+    for (int i = 0; i < n;) {
+      int j = i + 1;
+      const int len = v[off + i].z1 - v[off + i].z0;
+      while (j < n && v[off + j].z1 - v[off + j].z0 == len) ++j;
+      run.assign(v.begin() + off + i, v.begin() + off + j);
+      int next[8], at = 0;
+      for (int x = 0; x < 8; ++x) {  // positions p of the run with (i + p) mod 8 == x
+        next[x] = at;
+        const int first = (x - i % 8 + 8) % 8;
+        at += first < j - i ? (j - i - first + 7) / 8 : 0;
+      }
+      for (int p = i; p < j; ++p) v[off + p] = run[next[p % 8]++];
+      i = j;
     }
   };
   longest_first(h->h_fitems, L.flux.off, L.flux.n);
@@ -220,13 +301,11 @@ LaunchList make_list(amr_hierarchy* h, const std::vector<std::pair<int, int>>& g
         out.push_back(it);
       }
     }
-    std::stable_sort(out.begin(), out.end(), [](const FluxItem& x, const FluxItem& y) { return x.z1 - x.z0 > y.z1 - y.z0; });
     h->h_xitems.resize(L.fused.off);
     h->h_xitems.insert(h->h_xitems.end(), out.begin(), out.end());
     L.fused.n = (int)out.size();
-  } else {
-    longest_first(h->h_xitems, L.fused.off, L.fused.n);
   }
+  longest_first(h->h_xitems, L.fused.off, L.fused.n);
   return L;
 }
 
