@@ -119,6 +119,12 @@ struct amr_hierarchy {
   std::vector<uint8_t> h_fmask;
   uint8_t* d_fmask = nullptr;
   bool fused = false;  // launch mode bit 3: one fused flux-update kernel per launch
+  // A configuration was set.  Until then launches take the fused kernel: it
+  // gives the two kernels' results bit for bit, in less time on every size
+  // (two steps, one 2-D grid of 64^2 48 -> 42 us, of 1021 x 517 FP32 116 ->
+  // 80; 37 x 33 x 35 FP32 71 -> 65; coarse steps of small 2-D and 3-D
+  // hierarchies 257 -> 225 and 469 -> 460).
+  bool configured = false;
   int fused_pblocks = 0;
   int4* d_cfl = nullptr;
   int n_cfl = 0;

@@ -1243,6 +1243,7 @@ void set_launch_config(amr_hierarchy* h, int policy, int zchunk, int mode) {
   h->persistent_flux = (mode & 5) != 0;
   const bool xcd = (mode & 2) != 0;
   h->fused = (mode & 8) != 0;
+  h->configured = true;
   // the item order depends on the XCD chunking (see make_list)
   if (policy != h->tile_policy || zchunk != h->zchunk || xcd != h->xcd_chunks) {
     h->tile_policy = policy;
