@@ -11,9 +11,18 @@
 //   k_adj_prim   per cell: adjoint of the minmod slopes (frozen choices) and
 //                of the primitive recovery                      -> AU
 //   k_adj_assemble  per element: identity part of the update plus every
-//                contribution above                             -> TMP
+//                contribution above; own elements -> lambda, band ones -> TMP
 //   k_adj_fold   transpose of the band copy: band adjoints are added to the
 //                interior elements they were copied from        -> lambda
+// They are bound by their memory traffic (142 arrays) and, the face and cell
+// reverses, by registers (one or two waves a SIMD).  64^3, FP64, a reverse
+// step: 257 us (pred 38, face 84, cell 70, prim 33, assemble 21, fold 11);
+// it was 338 with the slope choices formed again by k_adj_prim from the
+// states of 27 neighbours (100 us), one thread for a cell's three faces (87),
+// a copy of every own element (10) and the fields of k_adj_fold one after the
+// other (17).
+#include <type_traits>
+
 #include "adjoint_internal.hpp"
 #include "advance_common.hpp"
 #include "emf.hpp"
@@ -57,7 +66,8 @@ template <int NDIM> struct Reg {
 template <class T> struct AdjArrays {
   T* ps;  // predicted states: [(d*2+side)*7 + q] arrays
   T* af;  // per face direction: [d*15 + 0..6] a_WL, [+7..13] a_WR, [+14] a_Bn
-  T* ac;  // per cell: [0..7] a_Wpred, [8 + d*8 + q] a_slope, [32 + d*2 + side] a_face
+  T* ac;  // per cell: [0..7] a_W, [8 + d*8 + q] a_slope, [32 + d*2 + side] a_face; a_slope of the normal field
+          // (q = 5 + d), which has no slope, holds the slopes' choices instead
   T* au;  // per cell: [0..4] a_U hydro, [5] a_Bz cell (2D), [6 + d] a_Bbar
   T* tmp; // 8 assembled adjoint arrays
   int64_t stride;  // elements per array
@@ -67,6 +77,9 @@ template <class T> struct AdjArrays {
   }
   __device__ T& AF(int d, int c, int64_t e) const { return af[(int64_t)(d * 15 + c) * stride + (e - e0)]; }
   __device__ T& AC(int c, int64_t e) const { return ac[(int64_t)c * stride + (e - e0)]; }
+  // choices of direction d's slopes at a cell: bit q set where the slope of
+  // slot q is the difference to the low neighbour, bit 8 + q to the high one
+  __device__ uint32_t& CHOICE(int d, int64_t e) const { return *reinterpret_cast<uint32_t*>(&AC(8 + d * 8 + 5 + d, e)); }
   __device__ T& AU(int c, int64_t e) const { return au[(int64_t)c * stride + (e - e0)]; }
   __device__ T& TMP(int c, int64_t e) const { return tmp[(int64_t)c * stride + (e - e0)]; }
 };
@@ -181,10 +194,12 @@ __device__ __forceinline__ T edge_lambda(const GridDesc& G, const DevState<T>& L
   return v;
 }
 
+// (a grid row of blocks per direction: three short launches in one, 84 us on
+// 64^3 in FP64 against 87 for the three in turn)
 template <class T, int NDIM>
-__global__ __launch_bounds__(256) void k_adj_face(const GridDesc* __restrict__ grids, const int2* __restrict__ items,
-                                                  int nitems, DevState<T> U, DevState<T> Lp, AdjArrays<T> A,
-                                                  double dt0, Phys ph) {
+__global__ __launch_bounds__(256, 2) void k_adj_face(const GridDesc* __restrict__ grids,
+                                                     const int2* __restrict__ items, int nitems, DevState<T> U,
+                                                     DevState<T> Lp, AdjArrays<T> A, double dt0, Phys ph) {
   const T gam = T(ph.gamma);
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const int2 item = items[it];
@@ -196,8 +211,8 @@ __global__ __launch_bounds__(256) void k_adj_face(const GridDesc* __restrict__ g
     const T cdt[3] = {ls.dt * ls.idx[0], ls.dt * ls.idx[1], ls.dt * ls.idx[2]};
     const int64_t st[3] = {1, G.P[0], NDIM == 3 ? (int64_t)G.P[0] * G.P[1] : 0};
     const int x[3] = {p.i, p.j, p.k};
-#pragma unroll
-    for (int d = 0; d < NDIM; ++d) {
+    auto face = [&](auto dir) {
+      constexpr int d = decltype(dir)::value;
       // flux faces: normal index [0, n], transverse [-1, n]
       bool ok = true;
 #pragma unroll
@@ -206,7 +221,7 @@ __global__ __launch_bounds__(256) void k_adj_face(const GridDesc* __restrict__ g
         const int hi = G.n[a] + 1;
         ok = ok && x[a] >= lo && x[a] < hi;
       }
-      if (!ok) continue;
+      if (!ok) return;
       int xm[3] = {x[0], x[1], x[2]};
       xm[d] -= 1;
       const bool oc = own_cell<T, NDIM>(G, x[0], x[1], x[2]);
@@ -279,7 +294,10 @@ __global__ __launch_bounds__(256) void k_adj_face(const GridDesc* __restrict__ g
       A.AF(d, 12, p.e) = aqr[6];
       A.AF(d, 13, p.e) = aqr[7];
       A.AF(d, 14, p.e) = abn;
-    }
+    };
+    if (blockIdx.y == 0) face(std::integral_constant<int, 0>());
+    else if (blockIdx.y == 1) face(std::integral_constant<int, 1>());
+    else if constexpr (NDIM == 3) face(std::integral_constant<int, 2>());
   }
 }
 
@@ -297,6 +315,10 @@ __device__ __forceinline__ void unrotate7(const T (&q)[7], T (&w)[8]) {
   w[5 + (D + 2) % 3] = q[6];
 }
 
+// What is carried from the forward values to the reverse is the slopes and
+// the increment (the face states are formed again from them) and, of the face
+// states' adjoints, their sums into a_W and the slopes.  One wave a SIMD:
+// compiled for two it spills and takes 105 us instead of 70 (64^3, FP64).
 template <class T, int NDIM>
 __global__ __launch_bounds__(256) void k_adj_cell(const GridDesc* __restrict__ grids, const int2* __restrict__ items,
                                                   int nitems, DevState<T> U, AdjArrays<T> A, double dt0, Phys ph) {
@@ -311,52 +333,68 @@ __global__ __launch_bounds__(256) void k_adj_cell(const GridDesc* __restrict__ g
     const Idx<NDIM> ix(G);
     const int64_t st[3] = {1, ix.sy, NDIM == 3 ? ix.sz : 0};
     const int x[3] = {p.i, p.j, p.k};
-    // forward recompute: W, slopes, face states, increment
-    T w[8], nb[3][2][8];
+    // forward recompute: W, slopes and their choices, increment
+    T w[8], sl[3][8], du[8], fb[3][2];
+    uint32_t choice[3] = {0u, 0u, 0u};
     load_prim<T, NDIM>(U, p.e, ix.sy, ix.sz, gm1, w);
 #pragma unroll
     for (int d = 0; d < NDIM; ++d) {
-      load_prim<T, NDIM>(U, p.e - st[d], ix.sy, ix.sz, gm1, nb[d][0]);
-      load_prim<T, NDIM>(U, p.e + st[d], ix.sy, ix.sz, gm1, nb[d][1]);
-    }
-    T sl[3][8], ws[3][2][8], fb[3][2];
-#pragma unroll
-    for (int d = 0; d < NDIM; ++d) {
+      T lo[8], hi[8];
+      load_prim<T, NDIM>(U, p.e - st[d], ix.sy, ix.sz, gm1, lo);
+      load_prim<T, NDIM>(U, p.e + st[d], ix.sy, ix.sz, gm1, hi);
       fb[d][0] = U.f[5 + d][p.e];
       fb[d][1] = U.f[5 + d][p.e + st[d]];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) sl[d][q] = limiter_minmod(w[q] - nb[d][0][q], nb[d][1][q] - w[q]);
-#pragma unroll
       for (int q = 0; q < 8; ++q) {
-        ws[d][0][q] = w[q] - T(0.5) * sl[d][q];
-        ws[d][1][q] = w[q] + T(0.5) * sl[d][q];
+        const T a = w[q] - lo[q], b = hi[q] - w[q];
+        sl[d][q] = limiter_minmod(a, b);
+        choice[d] |= sl[d][q] != T(0) ? (dabs(b) < dabs(a) ? 256u : 1u) << q : 0u;
       }
-      ws[d][0][5 + d] = fb[d][0];
-      ws[d][1][5 + d] = fb[d][1];
     }
-    T du[8];
+    // face state of direction d, side s (s = +-1)
+    auto face_state = [&](int d, int side, T (&ws)[8]) {
+      const T h = side ? T(0.5) : T(-0.5);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) ws[q] = w[q] + h * sl[d][q];
+      ws[5 + d] = fb[d][side];
+    };
 #pragma unroll
     for (int q = 0; q < 8; ++q) du[q] = T(0);
 #pragma unroll
     for (int d = 0; d < NDIM; ++d) {
-      T fl[8], fr[8];
-      if (d == 0) { flux_along<0>(ws[d][0], fl, gm1_inv); flux_along<0>(ws[d][1], fr, gm1_inv); }
-      else if (d == 1) { flux_along<1>(ws[d][0], fl, gm1_inv); flux_along<1>(ws[d][1], fr, gm1_inv); }
-      else { flux_along<2>(ws[d][0], fl, gm1_inv); flux_along<2>(ws[d][1], fr, gm1_inv); }
+      T wl[8], wr[8], fl[8], fr[8];
+      face_state(d, 0, wl);
+      face_state(d, 1, wr);
+      if (d == 0) { flux_along<0>(wl, fl, gm1_inv); flux_along<0>(wr, fr, gm1_inv); }
+      else if (d == 1) { flux_along<1>(wl, fl, gm1_inv); flux_along<1>(wr, fr, gm1_inv); }
+      else { flux_along<2>(wl, fl, gm1_inv); flux_along<2>(wr, fr, gm1_inv); }
       const T c = cd[d];
 #pragma unroll
       for (int q = 0; q < 8; ++q) du[q] -= c * (fr[q] - fl[q]);
     }
-    // reverse: predicted states
-    T a_ws[3][2][8], a_du[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) a_du[q] = T(0);
+    for (int d = 0; d < NDIM; ++d) form_now(sl[d]);
+    form_now(du);
+    asm volatile("" ::: "memory");  // (the loads below are not moved up: no registers for them there)
+    // reverse: predicted states
+    T a_w[8], a_sl[3][8], a_fb[3][2], a_du[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) a_w[q] = a_du[q] = a_sl[0][q] = a_sl[1][q] = a_sl[2][q] = T(0);
+    // adjoint of a face state into a_W, the slopes and the face field
+    auto spread = [&](int d, int side, const T (&a_ws)[8]) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        if (q == 5 + d) continue;
+        a_w[q] += a_ws[q];
+        a_sl[d][q] += side ? T(0.5) * a_ws[q] : -T(0.5) * a_ws[q];
+      }
+      a_fb[d][side] += a_ws[5 + d];
+    };
 #pragma unroll
     for (int d = 0; d < NDIM; ++d)
 #pragma unroll
       for (int side = 0; side < 2; ++side) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) a_ws[d][side][q] = T(0);
+        a_fb[d][side] = T(0);
         // adjoint of the predicted state (d, side) from its face
         int y[3] = {x[0], x[1], x[2]};
         if (side == 1) y[d] += 1;
@@ -375,49 +413,61 @@ __global__ __launch_bounds__(256) void k_adj_cell(const GridDesc* __restrict__ g
         if (d == 0) unrotate7<0>(a7, a_wb);
         else if (d == 1) unrotate7<1>(a7, a_wb);
         else unrotate7<2>(a7, a_wb);
-        T us[8], ubar[8];
-        to_conserved(ws[d][side], us, gm1_inv);
+        T ws[8], us[8], ubar[8];
+        face_state(d, side, ws);
+        to_conserved(ws, us, gm1_inv);
 #pragma unroll
         for (int q = 0; q < 8; ++q) ubar[q] = us[q] + du[q];
-        T a_ub[8];
+        T a_ub[8], a_ws[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) a_ub[q] = T(0);
+        for (int q = 0; q < 8; ++q) a_ub[q] = a_ws[q] = T(0);
         to_primitive_adj(ubar, gm1, a_wb, a_ub);
 #pragma unroll
         for (int q = 0; q < 8; ++q) a_du[q] += a_ub[q];
-        to_conserved_adj(ws[d][side], gm1_inv, a_ub, a_ws[d][side]);
+        to_conserved_adj(ws, gm1_inv, a_ub, a_ws);
+        spread(d, side, a_ws);
+        if (side == 1) {
+          form_now(a_w);
+          form_now(a_sl[d]);
+          form_now(a_du);
+          form_now(w);
+          asm volatile("" ::: "memory");
+        }
       }
+#pragma unroll
+    for (int d = 0; d < NDIM; ++d) form_now(sl[d]);
     // reverse: increment du = -sum_d c_d (F_d(w+) - F_d(w-))
 #pragma unroll
-    for (int d = 0; d < NDIM; ++d) {
-      T afr[8], afl[8];
+    for (int d = 0; d < NDIM; ++d)
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        afr[q] = -cd[d] * a_du[q];
-        afl[q] = cd[d] * a_du[q];
+      for (int side = 0; side < 2; ++side) {
+        T ws[8], af[8], a_ws[8];
+        face_state(d, side, ws);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          af[q] = side ? -cd[d] * a_du[q] : cd[d] * a_du[q];
+          a_ws[q] = T(0);
+        }
+        if (d == 0) flux_along_adj<0>(ws, gm1_inv, af, a_ws);
+        else if (d == 1) flux_along_adj<1>(ws, gm1_inv, af, a_ws);
+        else flux_along_adj<2>(ws, gm1_inv, af, a_ws);
+        spread(d, side, a_ws);
       }
-      if (d == 0) { flux_along_adj<0>(ws[d][1], gm1_inv, afr, a_ws[d][1]); flux_along_adj<0>(ws[d][0], gm1_inv, afl, a_ws[d][0]); }
-      else if (d == 1) { flux_along_adj<1>(ws[d][1], gm1_inv, afr, a_ws[d][1]); flux_along_adj<1>(ws[d][0], gm1_inv, afl, a_ws[d][0]); }
-      else { flux_along_adj<2>(ws[d][1], gm1_inv, afr, a_ws[d][1]); flux_along_adj<2>(ws[d][0], gm1_inv, afl, a_ws[d][0]); }
-    }
-    // reverse: face states W +- slope/2 (normal B from the faces)
-    T a_w[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) a_w[q] = T(0);
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-#pragma unroll
-      for (int q = 0; q < 8; ++q) A.AC(8 + d * 8 + q, p.e) = T(0);
+    // the cell's own share of its slopes' adjoints is added here, the
+    // neighbours' shares go out with the choices (slope = W(c) - W(c - e_d)
+    // or W(c + e_d) - W(c))
 #pragma unroll
     for (int d = 0; d < NDIM; ++d) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         if (q == 5 + d) continue;
-        a_w[q] += a_ws[d][0][q] + a_ws[d][1][q];
-        A.AC(8 + d * 8 + q, p.e) = T(0.5) * (a_ws[d][1][q] - a_ws[d][0][q]);
+        const T as = a_sl[d][q];
+        a_w[q] += ((choice[d] >> q) & 1u) ? as : ((choice[d] >> (8 + q)) & 1u) ? -as : T(0);
+        A.AC(8 + d * 8 + q, p.e) = as;
       }
-      A.AC(32 + d * 2 + 0, p.e) = a_ws[d][0][5 + d];
-      A.AC(32 + d * 2 + 1, p.e) = a_ws[d][1][5 + d];
+      A.CHOICE(d, p.e) = choice[d];
+      A.AC(32 + d * 2 + 0, p.e) = a_fb[d][0];
+      A.AC(32 + d * 2 + 1, p.e) = a_fb[d][1];
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q) A.AC(q, p.e) = a_w[q];
@@ -441,35 +491,21 @@ __global__ __launch_bounds__(256) void k_adj_prim(const GridDesc* __restrict__ g
     const bool pred_here = Reg<NDIM>::cells(G, x[0], x[1], x[2], 1);
 #pragma unroll
     for (int q = 0; q < 8; ++q) a_w[q] = pred_here ? A.AC(q, p.e) : T(0);
-    // slopes of the cells c' = c - e_d, c, c + e_d use W(c)
+    // the slopes of the neighbours c -+ e_d that were formed with W(c): the
+    // high difference of the low neighbour, the low one of the high neighbour
 #pragma unroll
     for (int d = 0; d < NDIM; ++d) {
+      int lo[3] = {x[0], x[1], x[2]}, hi[3] = {x[0], x[1], x[2]};
+      lo[d] -= 1;
+      hi[d] += 1;
+      const int64_t el = p.e - st[d], eh = p.e + st[d];
+      const uint32_t cl = Reg<NDIM>::cells(G, lo[0], lo[1], lo[2], 1) ? A.CHOICE(d, el) : 0u;
+      const uint32_t ch = Reg<NDIM>::cells(G, hi[0], hi[1], hi[2], 1) ? A.CHOICE(d, eh) : 0u;
 #pragma unroll
-      for (int o = -1; o <= 1; ++o) {
-        int y[3] = {x[0], x[1], x[2]};
-        y[d] += o;
-        if (!Reg<NDIM>::cells(G, y[0], y[1], y[2], 1)) continue;
-        const int64_t ec = p.e + o * st[d];
-        T wm[8], wc[8], wp[8];
-        load_prim<T, NDIM>(U, ec - st[d], ix.sy, ix.sz, gm1, wm);
-        load_prim<T, NDIM>(U, ec, ix.sy, ix.sz, gm1, wc);
-        load_prim<T, NDIM>(U, ec + st[d], ix.sy, ix.sz, gm1, wp);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          if (q == 5 + d) continue;
-          const T a = wc[q] - wm[q], b = wp[q] - wc[q];
-          if (!(a * b > T(0))) continue;
-          const bool pick_b = dabs(b) < dabs(a);
-          const T as = A.AC(8 + d * 8 + q, ec);
-          // slope = a = W(c') - W(c'-e_d), or b = W(c'+e_d) - W(c')
-          if (!pick_b) {
-            if (o == 0) a_w[q] += as;       // c' = c
-            else if (o == 1) a_w[q] -= as;  // c = c' - e_d
-          } else {
-            if (o == -1) a_w[q] += as;      // c = c' + e_d
-            else if (o == 0) a_w[q] -= as;  // c' = c
-          }
-        }
+      for (int q = 0; q < 8; ++q) {
+        if (q == 5 + d) continue;
+        if ((cl >> (8 + q)) & 1u) a_w[q] += A.AC(8 + d * 8 + q, el);
+        if ((ch >> q) & 1u) a_w[q] -= A.AC(8 + d * 8 + q, eh);
       }
     }
     // primitive recovery with cell-centred B
@@ -498,7 +534,7 @@ __global__ __launch_bounds__(256) void k_adj_prim(const GridDesc* __restrict__ g
 template <class T, int NDIM>
 __global__ __launch_bounds__(256) void k_adj_assemble(const GridDesc* __restrict__ grids,
                                                       const int2* __restrict__ items, int nitems, DevState<T> Lp,
-                                                      AdjArrays<T> A) {
+                                                      AdjArrays<T> A, DevState<T> Lout) {
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const int2 item = items[it];
     const GridDesc G = grids[item.x];
@@ -517,7 +553,8 @@ __global__ __launch_bounds__(256) void k_adj_assemble(const GridDesc* __restrict
       const int s = slots[t];
       T v = oc ? Lp.f[s][p.e] : T(0);
       if (wc) v += A.AU(t, p.e);
-      A.TMP(s, p.e) = v;
+      Lout.f[s][p.e] = oc ? v : T(0);
+      if (!oc) A.TMP(s, p.e) = v;
     }
     // faces
 #pragma unroll
@@ -525,7 +562,8 @@ __global__ __launch_bounds__(256) void k_adj_assemble(const GridDesc* __restrict
       int xm[3] = {x[0], x[1], x[2]};
       xm[d] -= 1;
       // inside the padded box the face index runs to n+g
-      T v = own_face<T, NDIM>(G, d, x[0], x[1], x[2]) ? Lp.f[5 + d][p.e] : T(0);
+      const bool of = own_face<T, NDIM>(G, d, x[0], x[1], x[2]);
+      T v = of ? Lp.f[5 + d][p.e] : T(0);
       bool flux = true;
 #pragma unroll
       for (int a = 0; a < NDIM; ++a) {
@@ -537,54 +575,26 @@ __global__ __launch_bounds__(256) void k_adj_assemble(const GridDesc* __restrict
       if (Reg<NDIM>::cells(G, xm[0], xm[1], xm[2], 1)) v += A.AC(32 + d * 2 + 1, p.e - st[d]);
       if (Reg<NDIM>::cells(G, x[0], x[1], x[2], 2)) v += T(0.5) * A.AU(6 + d, p.e);
       if (Reg<NDIM>::cells(G, xm[0], xm[1], xm[2], 2)) v += T(0.5) * A.AU(6 + d, p.e - st[d]);
-      A.TMP(5 + d, p.e) = v;
+      Lout.f[5 + d][p.e] = of ? v : T(0);
+      if (!of) A.TMP(5 + d, p.e) = v;
     }
   }
 }
 
 // ----------------------------------------------------------- K6 fold
 template <class T, int NDIM>
-__global__ __launch_bounds__(256) void k_adj_own(const GridDesc* __restrict__ grids, const int2* __restrict__ items,
-                                                 int nitems, AdjArrays<T> A, DevState<T> Lout) {
-  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const int2 item = items[it];
-    const GridDesc G = grids[item.x];
-    const ElemPos p = elem_pos<NDIM>(G, item.y + threadIdx.x);
-    if (!p.ok) continue;
-    const bool oc = own_cell<T, NDIM>(G, p.i, p.j, p.k);
-    const int slots[6] = {0, 1, 2, 3, 4, 7};
-    const int ns = NDIM == 2 ? 6 : 5;
-#pragma unroll
-    for (int t = 0; t < 6; ++t) {
-      if (t >= ns) break;
-      Lout.f[slots[t]][p.e] = oc ? A.TMP(slots[t], p.e) : T(0);
-    }
-#pragma unroll
-    for (int d = 0; d < NDIM; ++d)
-      Lout.f[5 + d][p.e] = own_face<T, NDIM>(G, d, p.i, p.j, p.k) ? A.TMP(5 + d, p.e) : T(0);
-  }
-}
-
-template <class T, int NDIM>
 __global__ __launch_bounds__(256) void k_adj_fold(const InvCopy* __restrict__ inv, int n,
                                                   const int32_t* __restrict__ dsts, AdjArrays<T> A,
                                                   DevState<T> Lout) {
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
     const InvCopy c = inv[t];
-    if (c.cls == 0) {
-      const int slots[6] = {0, 1, 2, 3, 4, 7};
-      const int ns = NDIM == 2 ? 6 : 5;
-      for (int q = 0; q < ns; ++q) {
-        T acc = T(0);
-        for (int i = c.begin; i < c.end; ++i) acc += A.TMP(slots[q], dsts[i]);
-        Lout.f[slots[q]][c.src] += acc;
-      }
-    } else {
-      const int s = 4 + c.cls;
-      T acc = T(0);
-      for (int i = c.begin; i < c.end; ++i) acc += A.TMP(s, dsts[i]);
-      Lout.f[s][c.src] += acc;
-    }
+    // cell entries: field y of blockIdx.y; face entries: their one field, row 0
+    const int y = (int)blockIdx.y;
+    if (c.cls != 0 && y != 0) continue;
+    const int s = c.cls != 0 ? 4 + c.cls : y < 5 ? y : 7;
+    T acc = T(0);
+    for (int i = c.begin; i < c.end; ++i) acc += A.TMP(s, dsts[i]);
+    Lout.f[s][c.src] += acc;
   }
 }
 
@@ -667,22 +677,20 @@ void launch_adjoint_step(int ndim, const GridDesc* grids, const int2* items, int
   const dim3 grid(nitems), block(256);
   if (ndim == 3) {
     hipLaunchKernelGGL((k_adj_pred<T, 3>), grid, block, 0, s, grids, items, nitems, U, A, dt0, ph);
-    hipLaunchKernelGGL((k_adj_face<T, 3>), grid, block, 0, s, grids, items, nitems, U, Lp, A, dt0, ph);
+    hipLaunchKernelGGL((k_adj_face<T, 3>), dim3(nitems, 3), block, 0, s, grids, items, nitems, U, Lp, A, dt0, ph);
     hipLaunchKernelGGL((k_adj_cell<T, 3>), grid, block, 0, s, grids, items, nitems, U, A, dt0, ph);
     hipLaunchKernelGGL((k_adj_prim<T, 3>), grid, block, 0, s, grids, items, nitems, U, A, ph);
-    hipLaunchKernelGGL((k_adj_assemble<T, 3>), grid, block, 0, s, grids, items, nitems, Lp, A);
-    hipLaunchKernelGGL((k_adj_own<T, 3>), grid, block, 0, s, grids, items, nitems, A, Lout);
+    hipLaunchKernelGGL((k_adj_assemble<T, 3>), grid, block, 0, s, grids, items, nitems, Lp, A, Lout);
     if (ninv > 0)
-      hipLaunchKernelGGL((k_adj_fold<T, 3>), dim3(blocks_for(ninv)), block, 0, s, inv, ninv, dsts, A, Lout);
+      hipLaunchKernelGGL((k_adj_fold<T, 3>), dim3(blocks_for(ninv), 5), block, 0, s, inv, ninv, dsts, A, Lout);
   } else {
     hipLaunchKernelGGL((k_adj_pred<T, 2>), grid, block, 0, s, grids, items, nitems, U, A, dt0, ph);
-    hipLaunchKernelGGL((k_adj_face<T, 2>), grid, block, 0, s, grids, items, nitems, U, Lp, A, dt0, ph);
+    hipLaunchKernelGGL((k_adj_face<T, 2>), dim3(nitems, 2), block, 0, s, grids, items, nitems, U, Lp, A, dt0, ph);
     hipLaunchKernelGGL((k_adj_cell<T, 2>), grid, block, 0, s, grids, items, nitems, U, A, dt0, ph);
     hipLaunchKernelGGL((k_adj_prim<T, 2>), grid, block, 0, s, grids, items, nitems, U, A, ph);
-    hipLaunchKernelGGL((k_adj_assemble<T, 2>), grid, block, 0, s, grids, items, nitems, Lp, A);
-    hipLaunchKernelGGL((k_adj_own<T, 2>), grid, block, 0, s, grids, items, nitems, A, Lout);
+    hipLaunchKernelGGL((k_adj_assemble<T, 2>), grid, block, 0, s, grids, items, nitems, Lp, A, Lout);
     if (ninv > 0)
-      hipLaunchKernelGGL((k_adj_fold<T, 2>), dim3(blocks_for(ninv)), block, 0, s, inv, ninv, dsts, A, Lout);
+      hipLaunchKernelGGL((k_adj_fold<T, 2>), dim3(blocks_for(ninv), 6), block, 0, s, inv, ninv, dsts, A, Lout);
   }
 }
 

@@ -156,6 +156,14 @@ __device__ __forceinline__ void raw3_to_prim(const T (&r)[5], const T (&fb)[3][2
   to_primitive(u, w, gm1);
 }
 
+// Values that are formed here: neither sunk past a barrier to where they are
+// used (their inputs would be held in registers instead, which are scarcer),
+// nor what is derived from them before kept for after.
+template <class T, int N> __device__ __forceinline__ void form_now(T (&a)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(a[i]));
+}
+
 __device__ __forceinline__ void flag_bad(ErrBlock* err, int64_t e) {
   unsigned old = atomicOr(&err->flags, 1u);
   if ((old & 1u) == 0u) atomicExch((unsigned long long*)&err->first_bad, (unsigned long long)e);

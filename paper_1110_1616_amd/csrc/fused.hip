@@ -234,13 +234,6 @@ __global__ __launch_bounds__(256) void k_fused2(const GridDesc* __restrict__ gri
   retire<PERSIST>(q);
 }
 
-// Values that are formed here and not sunk past a barrier to where they are
-// used (their inputs would be held in registers instead, which are scarcer).
-template <class T, int N> __device__ __forceinline__ void form_now(T (&a)[N]) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(a[i]));
-}
-
 // 3-D: the tile marches along z.  Two blocks share a CU.
 template <class T, bool PERSIST>
 __global__ __launch_bounds__(256, (sizeof(T) == 8 ? 2 : 3)) void k_fused3(

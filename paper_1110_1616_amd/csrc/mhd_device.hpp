@@ -158,7 +158,7 @@ __host__ __forceinline__ float pmax(float a, float b) { return a < b ? b : a; }
 // spelled out; 24 of them a cell.
 template <class T> __host__ __device__ __forceinline__ T limiter_minmod(T a, T b) {
   T r = (dabs(b) < dabs(a)) ? b : a;
-  return (a * b > T(0)) ? r : T(0);
+  return ((a > T(0) && b > T(0)) || (a < T(0) && b < T(0))) ? r : T(0);
 }
 __device__ __forceinline__ double limiter_minmod(double a, double b) {
   return pmax(pmin(a, b), pmin(pmax(a, b), 0.0));
