@@ -118,10 +118,8 @@ void adjoint_run(amr_hierarchy* h, int level, int nsteps, const double* dts, con
   HIPCHK(hipGetLastError());
   // forward recompute of the segment's step inputs; band elements that the
   // same-level copy does not fill keep the checkpoint's values
-  for (int k = 0; k < nsteps; ++k) {
-    amr_state sk = state_at(k);
-    for (int q = 0; q < 8; ++q) HIPCHK(hipMemcpyAsync(sk.f[q], Uc->f[q], arr, hipMemcpyDeviceToDevice, s));
-  }
+  launch_replicate<T>(dstate<T>(Uc), base + a.off_states, arr, a.state_bytes, nsteps, t.e0, t.e1, s);
+  HIPCHK(hipGetLastError());
   const bool timing = h->timing;
   h->timing = false;
   for (int k = 0; k < nsteps; ++k) {

@@ -49,6 +49,12 @@ void launch_store_adj(int ndim, const GridDesc& G, Ptr8 g, DevState<T> L, hipStr
 template <class T>
 void launch_load_prim_adj(int ndim, const GridDesc& G, Ptr8 prim, DevState<T> L, MutPtr8 out, hipStream_t s);
 
+// Elements [e0, e1) of the eight arrays of nstates states, the first at base
+// and each state_bytes on (arrays array_bytes apart), <- those of src.
+template <class T>
+void launch_replicate(DevState<T> src, void* base, int64_t array_bytes, int64_t state_bytes, int nstates, int64_t e0,
+                      int64_t e1, hipStream_t s);
+
 // dst[0, n) <- host[0, n), passed by value in kernel arguments (no host
 // memory is read after the call returns).
 void launch_put_values(double* dst, const double* host, int n, hipStream_t s);
