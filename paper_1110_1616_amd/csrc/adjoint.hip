@@ -14,13 +14,13 @@
 //                contribution above; own elements -> lambda, band ones -> TMP
 //   k_adj_fold   transpose of the band copy: band adjoints are added to the
 //                interior elements they were copied from        -> lambda
-// They are bound by their memory traffic (142 arrays) and, the face and cell
+// They are bound by their memory traffic (87 arrays) and, the face and cell
 // reverses, by registers (one or two waves a SIMD).  64^3, FP64, a reverse
-// step: 257 us (pred 38, face 84, cell 70, prim 33, assemble 21, fold 11);
+// step: 251 us (pred 39, face 84, cell 69, prim 29, assemble 20, fold 10);
 // it was 338 with the slope choices formed again by k_adj_prim from the
 // states of 27 neighbours (100 us), one thread for a cell's three faces (87),
-// a copy of every own element (10) and the fields of k_adj_fold one after the
-// other (17).
+// a copy of every own element (10), the fields of k_adj_fold one after the
+// other (17) and 142 arrays that shared nothing.
 #include <type_traits>
 
 #include "adjoint_internal.hpp"

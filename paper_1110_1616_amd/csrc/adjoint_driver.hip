@@ -137,9 +137,9 @@ void adjoint_run(amr_hierarchy* h, int level, int nsteps, const double* dts, con
   const int64_t ab = a.stride * (int64_t)sizeof(T);
   buf.ps = base;
   buf.af = base + 42 * ab;
-  buf.ac = base + (42 + 45) * ab;
-  buf.au = base + (42 + 45 + 38) * ab;
-  buf.tmp = base + (42 + 45 + 38 + 9) * ab;
+  buf.ac = base;
+  buf.au = base + 42 * ab;
+  buf.tmp = base + (42 + 15) * ab;
   buf.stride = a.stride;
   buf.e0 = t.e0;
   amr_state other;
