@@ -89,42 +89,39 @@ __global__ __launch_bounds__(256) void k_registers(RegJobs<T> jobs, const GridDe
   }
 }
 
-// Reflux of one uncovered coarse cell.
+// Reflux of one uncovered coarse cell.  Every load of a register's fields is
+// issued before the first store of the cell's (one memory latency a register
+// instead of one a field).
 template <class T, int NDIM>
 __device__ __forceinline__ void reflux_one(const RefluxEntry& e, const T* __restrict__ reg, int nreg,
                                            const DevState<T>& U) {
   constexpr int ns = NDIM == 2 ? 6 : 5;
   constexpr int imax = 6;
-  {
+  T acc[ns];
 #pragma unroll
-    for (int q = 0; q < ns; ++q) {
-      const int s = q < 5 ? q : 7;
-      T acc = U.f[s][e.cell];
-      T rc[imax], rf[imax][kR];
+  for (int q = 0; q < ns; ++q) acc[q] = U.f[q < 5 ? q : 7][e.cell];
 #pragma unroll
-      for (int i = 0; i < imax; ++i) {
-        rc[i] = T(0);
+  for (int i = 0; i < imax; ++i)
+    if (i < e.n) {
+      const T* r = reg + (int64_t)e.reg[i] * 6;
+      T rc[ns], rf[ns][kR];
 #pragma unroll
-        for (int k = 0; k < kR; ++k) rf[i][k] = T(0);
-        if (i < e.n) {
-          const T* r = reg + (int64_t)e.reg[i] * 6 + q;
-          rc[i] = r[0];
+      for (int q = 0; q < ns; ++q) {
+        rc[q] = r[q];
 #pragma unroll
-          for (int k = 0; k < kR; ++k) rf[i][k] = r[(int64_t)(k + 1) * nreg * 6];
-        }
+        for (int k = 0; k < kR; ++k) rf[q][k] = r[(int64_t)(k + 1) * nreg * 6 + q];
       }
 #pragma unroll
-      for (int i = 0; i < imax; ++i)
-        if (i < e.n) {
-          T fine = T(0);
+      for (int q = 0; q < ns; ++q) {
+        T fine = T(0);
 #pragma unroll
-          for (int k = 0; k < kR; ++k) fine += rf[i][k];
-          const T delta = rc[i] - fine;
-          acc += T(e.coef[i]) * delta;
-        }
-      U.f[s][e.cell] = acc;
+        for (int k = 0; k < kR; ++k) fine += rf[q][k];
+        const T delta = rc[q] - fine;
+        acc[q] += T(e.coef[i]) * delta;
+      }
     }
-  }
+#pragma unroll
+  for (int q = 0; q < ns; ++q) U.f[q < 5 ? q : 7][e.cell] = acc[q];
 }
 
 // EMF correction of one copy of an uncovered coarse face.
