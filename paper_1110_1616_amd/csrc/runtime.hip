@@ -84,10 +84,9 @@ void run_list(amr_hierarchy* h, const LaunchList& L, const amr_state* Ua, const 
 // with level l-1, queued as jobs of one batched register launch.
 template <class T>
 void flush_registers(amr_hierarchy* h, RegJobs<T>& jobs, const double* dt0, void* ws, hipStream_t s) {
-  launch_register_jobs<T>(h->ndim, h->d_desc, jobs, dflux<T>(h, ws), dt0, h->upwind_emf, s);
+  launch_register_jobs<T>(h->ndim, jobs, dflux<T>(h, ws), dt0, h->upwind_emf, s);
   HIPCHK(hipGetLastError());
-  jobs.n = 0;
-  jobs.total = 0;
+  jobs.clear();
 }
 
 template <class T>
@@ -98,8 +97,7 @@ void add_registers(amr_hierarchy* h, int l, int k, const double* dt0, void* ws, 
     if (jobs.n == kMaxRegJobs) flush_registers<T>(h, jobs, dt0, ws, s);
     T* freg = (T*)((char*)ws + t.reg_off);
     T* ereg = (T*)((char*)ws + t.reg_off + ((int64_t)(1 + h->R) * t.nfreg * 6 * (int64_t)sizeof(T) + 255) / 256 * 256);
-    jobs.j[jobs.n++] = RegJob<T>{fe, ee, freg, ereg, nf, ne, t.nfreg, t.nereg, slot, jobs.total, div};
-    jobs.total += nf + ne;
+    jobs.add(RegJob<T>{fe, ee, freg, ereg, nf, ne, t.nfreg, t.nereg, slot, div});
   };
   if (l + 1 < h->nlev) {
     const SyncTables& t = h->sync[l + 1];

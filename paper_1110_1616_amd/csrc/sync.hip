@@ -23,69 +23,99 @@ inline int blocks_for(int64_t n) {
 // definition states (one memory latency per thread instead of one per term).
 constexpr int kR = 2;
 
-// Coarse/fine registers of one substep, both kinds in one launch: entries
-// [0, nf) are face registers, [nf, nf + ne) edge registers.
+// 1 / n of the n faces or edges a register averages: a power of the ratio,
+// so the product with it is the quotient, to the bit.
+template <class T> __device__ __forceinline__ T inv_count(int n) { return n == 1 ? T(1) : n == 2 ? T(0.5) : T(0.25); }
+
+// One face register: the cell-updating flux components at each of its faces,
+// all loads issued before the first use.  Component c of direction d carries
+// lab slot 1 + (c - 1 + d) mod 3 of the momenta, 2-D's cell field is component
+// 6 along x and 5 along y.
 template <class T, int NDIM>
 __device__ __forceinline__ void reg_face(const FaceRegEntry& e, const DevFlux<T>& F, T* __restrict__ reg, int nreg,
                                          int slot, T dt) {
   constexpr int ns = NDIM == 2 ? 6 : 5;
   constexpr int nmax = NDIM == 3 ? kR * kR : kR;
-  T* out = reg + ((int64_t)slot * nreg + e.reg) * 6;
-  T v[ns][nmax];
+  const char* fd = F.base + (uint64_t)(7 * e.d) * F.stride;
+  const char* fz = fd + (e.d == 0 ? 6 : 5) * F.stride;
+  T v[nmax][ns];
 #pragma unroll
-  for (int q = 0; q < ns; ++q) {
-    const int s = q < 5 ? q : 7;
-    const T* f = F.f[e.d][flux_comp(s, e.d)];
+  for (int i = 0; i < nmax; ++i) {
+    if (i < e.n) {
 #pragma unroll
-    for (int i = 0; i < nmax; ++i) v[q][i] = i < e.n ? f[e.e[i]] : T(0);
+      for (int q = 0; q < ns; ++q) v[i][q] = reinterpret_cast<const T*>(q < 5 ? fd + q * F.stride : fz)[e.e[i]];
+    } else {
+#pragma unroll
+      for (int q = 0; q < ns; ++q) v[i][q] = T(0);
+    }
   }
+  T* out = reg + ((int64_t)slot * nreg + e.reg) * 6;
+  const T inv = inv_count<T>(e.n);
 #pragma unroll
   for (int q = 0; q < ns; ++q) {
     T m = T(0);
 #pragma unroll
     for (int i = 0; i < nmax; ++i)
-      if (i < e.n) m += v[q][i];
-    out[q] = dt * (m / T(e.n));
+      if (i < e.n) m += v[i][q];
+    int s = q;
+    if (q >= 1 && q <= 3) {
+      s = q + e.d;
+      s = s > 3 ? s - 3 : s;
+    }
+    out[s] = dt * (m * inv);
   }
 }
 
-template <class T, int NDIM, bool UPWIND>
-__device__ __forceinline__ void reg_edge(const EdgeRegEntry& e, const GridDesc* __restrict__ grids,
-                                         const DevFlux<T>& F, T* __restrict__ reg, int nreg, int slot, T dt) {
-  const GridDesc G = grids[e.grid];
-  const int64_t st[3] = {1, G.P[0], NDIM == 3 ? (int64_t)G.P[0] * G.P[1] : 0};
-  T v[kR];
+template <class T, bool UPWIND>
+__device__ __forceinline__ void reg_edge(const EdgeRegEntry& e, const DevFlux<T>& F, T* __restrict__ reg, int nreg,
+                                         int slot, T dt) {
+  // faces of direction b = a + 1 (component 5) and c = a + 2 (component 6)
+  const int b = e.a == 2 ? 0 : e.a + 1, c = e.a == 0 ? 2 : e.a - 1;
+  const T* fb = reinterpret_cast<const T*>(F.base + (uint64_t)(7 * b + 5) * F.stride);
+  const T* fc = reinterpret_cast<const T*>(F.base + (uint64_t)(7 * c + 6) * F.stride);
+  const T* fe = UPWIND ? (e.a == 0 ? F.edge[0] : e.a == 1 ? F.edge[1] : F.edge[2]) : nullptr;
+  T v[kR][4];
 #pragma unroll
   for (int i = 0; i < kR; ++i) {
-    v[i] = T(0);
+    v[i][0] = v[i][1] = v[i][2] = v[i][3] = T(0);
     if (i < e.n) {
-      if (e.a == 0) v[i] = emf_at<0, UPWIND>(F, e.e[i], st);
-      else if (e.a == 1) v[i] = emf_at<1, UPWIND>(F, e.e[i], st);
-      else v[i] = emf_at<2, UPWIND>(F, e.e[i], st);
+      const int32_t x = e.e[i];
+      if (UPWIND) {
+        v[i][0] = fe[x];
+      } else {
+        v[i][0] = fb[x - e.st[1]];
+        v[i][1] = fb[x];
+        v[i][2] = fc[x - e.st[0]];
+        v[i][3] = fc[x];
+      }
     }
   }
   T m = T(0);
 #pragma unroll
   for (int i = 0; i < kR; ++i)
-    if (i < e.n) m += v[i];
-  reg[(int64_t)slot * nreg + e.reg] = dt * (m / T(e.n));
+    if (i < e.n) m += UPWIND ? v[i][0] : emf_mean(v[i][0], v[i][1], v[i][2], v[i][3]);
+  reg[(int64_t)slot * nreg + e.reg] = dt * (m * inv_count<T>(e.n));
 }
 
-// The face and edge registers of every job of a launch cycle in one launch:
-// thread t takes entry t - begin of the job whose range holds it, face
-// entries first, then edge entries.
+// The face and edge registers of every job of a launch cycle in one launch, a
+// thread an entry.  What bounds it is the chain of dependent loads: the job,
+// the entry, the fluxes.  A block lies in one job, so the job comes by scalar
+// loads; the flux arrays are reached by their common base and stride instead
+// of a pointer looked up by direction, and an edge's strides lie in its entry
+// (small hierarchy, 3 levels on 24^3 in FP64: 6.9 us a launch, 11.4 before; 2-D 64^2: 4.5, 8.1 before).
 template <class T, int NDIM, bool UPWIND>
-__global__ __launch_bounds__(256) void k_registers(RegJobs<T> jobs, const GridDesc* __restrict__ grids, DevFlux<T> F,
-                                                   const double* __restrict__ dt0p) {
+__global__ __launch_bounds__(kRegBlock) void k_registers(RegJobs<T> jobs, DevFlux<T> F,
+                                                         const double* __restrict__ dt0p) {
   const double dt0 = dt0p[0];
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < jobs.total; t += gridDim.x * blockDim.x) {
+  for (int blk = blockIdx.x; blk < jobs.blocks; blk += gridDim.x) {
     int j = 0;
-    while (j + 1 < jobs.n && t >= jobs.j[j + 1].begin) ++j;
+#pragma unroll
+    for (int k = 1; k < kMaxRegJobs; ++k) j += blk >= jobs.begin[k];
     const RegJob<T>& J = jobs.j[j];
     const T dt = T(dt0 / J.dt_div);
-    const int i = t - J.begin;
+    const int i = (blk - jobs.begin[j]) * kRegBlock + (int)threadIdx.x;
     if (i < J.nf) reg_face<T, NDIM>(J.fe[i], F, J.freg, J.nfreg, J.slot, dt);
-    else reg_edge<T, NDIM, UPWIND>(J.ee[i - J.nf], grids, F, J.ereg, J.nereg, J.slot, dt);
+    else if (i < J.nf + J.ne) reg_edge<T, UPWIND>(J.ee[i - J.nf], F, J.ereg, J.nereg, J.slot, dt);
   }
 }
 
@@ -228,11 +258,11 @@ __global__ __launch_bounds__(256) void k_sync(const RefluxEntry* __restrict__ rf
 }  // namespace
 
 template <class T>
-void launch_register_jobs(int ndim, const GridDesc* grids, const RegJobs<T>& jobs, DevFlux<T> F, const double* dt0,
-                          bool upwind_emf, hipStream_t s) {
-  if (jobs.total <= 0) return;
-#define AMR_REGS(ND, U) \
-  hipLaunchKernelGGL((k_registers<T, ND, U>), dim3(blocks_for(jobs.total)), dim3(256), 0, s, jobs, grids, F, dt0)
+void launch_register_jobs(int ndim, const RegJobs<T>& jobs, DevFlux<T> F, const double* dt0, bool upwind_emf,
+                          hipStream_t s) {
+  if (jobs.blocks <= 0) return;
+  const dim3 grid(jobs.blocks < 65535 ? jobs.blocks : 65535), block(kRegBlock);
+#define AMR_REGS(ND, U) hipLaunchKernelGGL((k_registers<T, ND, U>), grid, block, 0, s, jobs, F, dt0)
   if (ndim == 3) {
     if (upwind_emf) AMR_REGS(3, true);
     else AMR_REGS(3, false);
@@ -257,10 +287,10 @@ void launch_sync(int ndim, int R, const GridDesc* grids, const SyncTables& t, co
 #undef AMR_SYNC
 }
 
-template void launch_register_jobs<float>(int, const GridDesc*, const RegJobs<float>&, DevFlux<float>,
-                                          const double*, bool, hipStream_t);
-template void launch_register_jobs<double>(int, const GridDesc*, const RegJobs<double>&, DevFlux<double>,
-                                           const double*, bool, hipStream_t);
+template void launch_register_jobs<float>(int, const RegJobs<float>&, DevFlux<float>, const double*, bool,
+                                          hipStream_t);
+template void launch_register_jobs<double>(int, const RegJobs<double>&, DevFlux<double>, const double*, bool,
+                                           hipStream_t);
 template void launch_sync<float>(int, int, const GridDesc*, const SyncTables&, const float*, const float*,
                                  DevState<float>, DevState<float>, hipStream_t);
 template void launch_sync<double>(int, int, const GridDesc*, const SyncTables&, const double*, const double*,

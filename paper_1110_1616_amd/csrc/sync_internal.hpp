@@ -27,7 +27,7 @@ struct FaceRegEntry {  // register <- dt * mean of flux d at n elements of grid
 struct EdgeRegEntry {  // register <- dt * mean of EMF along axis a at n edges of grid
   int32_t reg, a, grid, n;
   int32_t e[2];
-  int32_t pad[2];
+  int32_t st[2];  // the grid's element strides along axes a + 1 and a + 2
 };
 struct RefluxEntry {  // cell += sum_i coef_i (reg_c - sum_k reg_f[k])
   int32_t cell, n;
@@ -68,26 +68,40 @@ struct SyncTables {
 };
 
 // Register writes of one side of one sync (slot 0: coarse, slot 1..R: fine
-// substep) from the face fluxes of the launch that just ran; the table of
-// entries [begin, begin + nf + ne) of a batched launch.
+// substep) from the face fluxes of the launch that just ran: nf face entries,
+// then ne edge entries.
 template <class T> struct RegJob {
   const FaceRegEntry* fe;
   const EdgeRegEntry* ee;
   T* freg;
   T* ereg;
-  int nf, ne, nfreg, nereg, slot, begin;
+  int nf, ne, nfreg, nereg, slot;
   double dt_div;  // level l steps dt0 / R^l
 };
 // Every register write that follows one launch cycle (the levels whose step
 // window ends there, both sides of each of their syncs): one kernel launch.
+// A job starts at a block of its own (the begin of those not in use lies past
+// every block), so that a block finds its job by scalar loads and compares.
 constexpr int kMaxRegJobs = 16;
+constexpr int kRegBlock = 256;
 template <class T> struct RegJobs {
+  int begin[kMaxRegJobs];  // first block
   RegJob<T> j[kMaxRegJobs];
-  int n = 0, total = 0;
+  int n = 0, blocks = 0;
+  RegJobs() { clear(); }
+  void clear() {
+    for (int& b : begin) b = INT32_MAX;
+    n = blocks = 0;
+  }
+  void add(const RegJob<T>& job) {
+    begin[n] = blocks;
+    j[n++] = job;
+    blocks += (job.nf + job.ne + kRegBlock - 1) / kRegBlock;
+  }
 };
 template <class T>
-void launch_register_jobs(int ndim, const GridDesc* grids, const RegJobs<T>& jobs, DevFlux<T> F, const double* dt0,
-                          bool upwind_emf, hipStream_t s);
+void launch_register_jobs(int ndim, const RegJobs<T>& jobs, DevFlux<T> F, const double* dt0, bool upwind_emf,
+                          hipStream_t s);
 
 // Reflux, EMF fix (coarse level state Uc) and restriction (fine Uf -> Uc).
 template <class T>

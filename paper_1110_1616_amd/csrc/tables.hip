@@ -1029,6 +1029,12 @@ void build_sync_tables(amr_hierarchy* h, int f) {
                     if (ea < nd) p[ea] += s2;
                     ef.e[ef.n++] = (int32_t)elem(h->desc[fg], nd, p[0], p[1], p[2]);
                   }
+                  for (EdgeRegEntry* r : {&ec, &ef}) {
+                    const GridDesc& G = h->desc[r->grid];
+                    const int32_t st[3] = {1, G.P[0], nd == 3 ? G.P[0] * G.P[1] : 0};
+                    r->st[0] = st[(ea + 1) % 3];
+                    r->st[1] = st[(ea + 2) % 3];
+                  }
                   out.edges.push_back(LocalEdge{key, ec, ef});
                 } else {
                   re = it->second;
