@@ -358,9 +358,8 @@ OverlapMaps build_overlap(const amr_hierarchy* hn, const amr_hierarchy* ho, int 
               for (int a = 0; a < nd; ++a)
                 if (cc[a] - PG.lo[a] < -P.g + 1 || cc[a] - PG.lo[a] > P.n[a] + P.g - 2)
                   throw Error(AMR_EINVAL, "internal: prolongation stencil leaves the parent box");
-              m.pc.push_back(ProlongEntry{(int32_t)dst,
-                                          (int32_t)elem(P, nd, cc[0] - PG.lo[0], cc[1] - PG.lo[1], cc[2] - PG.lo[2]),
-                                          pg, code});
+              m.pc.push_back(
+                  prolong_entry(dst, elem(P, nd, cc[0] - PG.lo[0], cc[1] - PG.lo[1], cc[2] - PG.lo[2]), P, nd, code));
               continue;
             }
             if (posmod(p[d], 2) == 1) continue;  // inside a coarse cell: projected
@@ -392,9 +391,8 @@ OverlapMaps build_overlap(const amr_hierarchy* hn, const amr_hierarchy* ho, int 
             int code = d;
             if (a1 < nd && posmod(p[a1], 2)) code |= 8;
             if (a2 < nd && posmod(p[a2], 2)) code |= 16;
-            m.pf.push_back(ProlongEntry{(int32_t)dst,
-                                        (int32_t)elem(P, nd, w[0] - PG.lo[0], w[1] - PG.lo[1], w[2] - PG.lo[2]), pg,
-                                        code});
+            m.pf.push_back(
+                prolong_entry(dst, elem(P, nd, w[0] - PG.lo[0], w[1] - PG.lo[1], w[2] - PG.lo[2]), P, nd, code));
           }
     }
     if (l == 0) return;
@@ -455,8 +453,8 @@ void do_overlap(amr_hierarchy* hn, int l, amr_state* Un, amr_state* Up, const am
     d_pj = dev_upload(M.pj);
     launch_copy2<T>(hn->ndim, d_cp, (int)M.cp.size(), M.cls, dstate<T>(Uo), dstate<T>(Un), s);
     if (l > 0) {
-      launch_prolong<T>(hn->ndim, d_pc, (int)M.pc.size(), d_pf, (int)M.pf.size(), hn->d_desc, dstate<T>(Up),
-                        dstate<T>(Un), phys(hn), s);
+      launch_prolong<T>(hn->ndim, d_pc, (int)M.pc.size(), d_pf, (int)M.pf.size(), dstate<T>(Up), dstate<T>(Un),
+                        phys(hn), l - 1, s);
       launch_project<T>(hn->ndim, d_pj, (int)M.pj.size(), hn->d_desc, dstate<T>(Un), phys(hn), s);
     }
     HIPCHK(hipGetLastError());

@@ -102,7 +102,8 @@ __device__ __forceinline__ void reg_edge(const EdgeRegEntry& e, const DevFlux<T>
 // the entry, the fluxes.  A block lies in one job, so the job comes by scalar
 // loads; the flux arrays are reached by their common base and stride instead
 // of a pointer looked up by direction, and an edge's strides lie in its entry
-// (small hierarchy, 3 levels on 24^3 in FP64: 6.9 us a launch, 11.4 before; 2-D 64^2: 4.5, 8.1 before).
+// (a launch on 3 levels over 24^3 in FP64: 6.9 us, 11.4 before; over 64^2:
+// 4.5 us, 8.1 before).
 template <class T, int NDIM, bool UPWIND>
 __global__ __launch_bounds__(kRegBlock) void k_registers(RegJobs<T> jobs, DevFlux<T> F,
                                                          const double* __restrict__ dt0p) {

@@ -604,9 +604,8 @@ void build_fill_maps(amr_hierarchy* h) {
                 for (int a = 0; a < nd; ++a)
                   if (cc[a] - PG.lo[a] < -P.g + 1 || cc[a] - PG.lo[a] > P.n[a] + P.g - 2)
                     throw Error(AMR_EINVAL, "internal: prolongation stencil leaves the parent box");
-                pc.push_back(ProlongEntry{(int32_t)dst,
-                                          (int32_t)elem(P, nd, cc[0] - PG.lo[0], cc[1] - PG.lo[1], cc[2] - PG.lo[2]),
-                                          pg, code});
+                pc.push_back(
+                    prolong_entry(dst, elem(P, nd, cc[0] - PG.lo[0], cc[1] - PG.lo[1], cc[2] - PG.lo[2]), P, nd, code));
               } else {
                 const int d = cls - 1;
                 const bool mid = posmod(gpos[d], 2) == 1;
@@ -640,9 +639,8 @@ void build_fill_maps(amr_hierarchy* h) {
                 int code = d | (mid ? 4 : 0);
                 if (a1 < nd && posmod(gpos[a1], 2)) code |= 8;
                 if (a2 < nd && posmod(gpos[a2], 2)) code |= 16;
-                pf.push_back(ProlongEntry{(int32_t)dst,
-                                          (int32_t)elem(P, nd, w[0] - PG.lo[0], w[1] - PG.lo[1], w[2] - PG.lo[2]), pg,
-                                          code});
+                pf.push_back(
+                    prolong_entry(dst, elem(P, nd, w[0] - PG.lo[0], w[1] - PG.lo[1], w[2] - PG.lo[2]), P, nd, code));
               }
             }
       }
