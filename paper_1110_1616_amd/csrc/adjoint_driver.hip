@@ -150,10 +150,8 @@ void adjoint_run(amr_hierarchy* h, int level, int nsteps, const double* dts, con
   const amr_state* Lp = lam;
   const amr_state* Lo = &other;
   if (nsteps % 2 == 1) {
-    const int64_t es = (int64_t)sizeof(T);
-    for (int q = 0; q < 8; ++q)
-      HIPCHK(hipMemcpyAsync((char*)other.f[q] + t.e0 * es, (const char*)lam->f[q] + t.e0 * es, (t.e1 - t.e0) * es,
-                            hipMemcpyDeviceToDevice, s));
+    launch_replicate<T>(dstate<T>(lam), base + a.off_lam, arr, 0, 1, t.e0, t.e1, s);
+    HIPCHK(hipGetLastError());
     Lp = &other;
     Lo = lam;
   }
