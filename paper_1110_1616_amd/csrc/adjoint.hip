@@ -16,7 +16,7 @@
 //                interior elements they were copied from        -> lambda
 // They are bound by their memory traffic (87 arrays) and, the face and cell
 // reverses, by registers (one or two waves a SIMD).  64^3, FP64, a reverse
-// step: 251 us (pred 39, face 84, cell 69, prim 29, assemble 20, fold 10);
+// step: 250 us (pred 36, face 84, cell 73, prim 27, assemble 20, fold 10);
 // it was 338 with the slope choices formed again by k_adj_prim from the
 // states of 27 neighbours (100 us), one thread for a cell's three faces (87),
 // a copy of every own element (10), the fields of k_adj_fold one after the
@@ -55,6 +55,15 @@ __device__ __forceinline__ ElemPos elem_pos(const GridDesc& G, int local) {
 }
 
 __device__ __forceinline__ bool in_range(int x, int lo, int hi) { return x >= lo && x < hi; }
+
+// Blocks reach the XCDs round-robin by their index.  Position b of a launch
+// takes the item that gives each XCD one contiguous eighth of the list, so a
+// chunk's neighbours (the planes above and below are 19 chunks away on a 64^3
+// grid) come from its own L2: prim 29.5 -> 26.6 us, pred 37.6 -> 36.2.  The
+// face and cell reverses keep the list's order: they wait for arithmetic, not
+// for those loads (cell 72 -> 78 us).
+__host__ __device__ __forceinline__ int xcd_positions(int n) { return ((n + 7) >> 3) << 3; }
+__device__ __forceinline__ int xcd_item(int b, int n) { return (b & 7) * ((n + 7) >> 3) + (b >> 3); }
 
 template <int NDIM> struct Reg {
   // cell regions for band-2 steps: W [-2, n+2), predicted [-1, n+1), own [0, n)
@@ -105,7 +114,9 @@ template <class T, int NDIM>
 __global__ __launch_bounds__(256) void k_adj_pred(const GridDesc* __restrict__ grids, const int2* __restrict__ items,
                                                   int nitems, DevState<T> U, AdjArrays<T> A, double dt0, Phys ph) {
   const T gm1 = T(ph.gamma) - T(1), gm1_inv = drcp(gm1);
-  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
+  for (int b = blockIdx.x; b < xcd_positions(nitems); b += gridDim.x) {
+    const int it = xcd_item(b, nitems);
+    if (it >= nitems) continue;
     const int2 item = items[it];
     const GridDesc G = grids[item.x];
     const ElemPos p = elem_pos<NDIM>(G, item.y + threadIdx.x);
@@ -479,7 +490,9 @@ template <class T, int NDIM>
 __global__ __launch_bounds__(256) void k_adj_prim(const GridDesc* __restrict__ grids, const int2* __restrict__ items,
                                                   int nitems, DevState<T> U, AdjArrays<T> A, Phys ph) {
   const T gam = T(ph.gamma), gm1 = gam - T(1);
-  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
+  for (int b = blockIdx.x; b < xcd_positions(nitems); b += gridDim.x) {
+    const int it = xcd_item(b, nitems);
+    if (it >= nitems) continue;
     const int2 item = items[it];
     const GridDesc G = grids[item.x];
     const ElemPos p = elem_pos<NDIM>(G, item.y + threadIdx.x);
@@ -535,7 +548,9 @@ template <class T, int NDIM>
 __global__ __launch_bounds__(256) void k_adj_assemble(const GridDesc* __restrict__ grids,
                                                       const int2* __restrict__ items, int nitems, DevState<T> Lp,
                                                       AdjArrays<T> A, DevState<T> Lout) {
-  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
+  for (int b = blockIdx.x; b < xcd_positions(nitems); b += gridDim.x) {
+    const int it = xcd_item(b, nitems);
+    if (it >= nitems) continue;
     const int2 item = items[it];
     const GridDesc G = grids[item.x];
     const ElemPos p = elem_pos<NDIM>(G, item.y + threadIdx.x);
@@ -688,21 +703,21 @@ void launch_adjoint_step(int ndim, const GridDesc* grids, const int2* items, int
   A.tmp = (T*)buf.tmp;
   A.stride = buf.stride;
   A.e0 = buf.e0;
-  const dim3 grid(nitems), block(256);
+  const dim3 grid(nitems), near(xcd_positions(nitems)), block(256);
   if (ndim == 3) {
-    hipLaunchKernelGGL((k_adj_pred<T, 3>), grid, block, 0, s, grids, items, nitems, U, A, dt0, ph);
+    hipLaunchKernelGGL((k_adj_pred<T, 3>), near, block, 0, s, grids, items, nitems, U, A, dt0, ph);
     hipLaunchKernelGGL((k_adj_face<T, 3>), dim3(nitems, 3), block, 0, s, grids, items, nitems, U, Lp, A, dt0, ph);
     hipLaunchKernelGGL((k_adj_cell<T, 3>), grid, block, 0, s, grids, items, nitems, U, A, dt0, ph);
-    hipLaunchKernelGGL((k_adj_prim<T, 3>), grid, block, 0, s, grids, items, nitems, U, A, ph);
-    hipLaunchKernelGGL((k_adj_assemble<T, 3>), grid, block, 0, s, grids, items, nitems, Lp, A, Lout);
+    hipLaunchKernelGGL((k_adj_prim<T, 3>), near, block, 0, s, grids, items, nitems, U, A, ph);
+    hipLaunchKernelGGL((k_adj_assemble<T, 3>), near, block, 0, s, grids, items, nitems, Lp, A, Lout);
     if (ninv > 0)
       hipLaunchKernelGGL((k_adj_fold<T, 3>), dim3(blocks_for(ninv), 5), block, 0, s, inv, ninv, dsts, A, Lout);
   } else {
-    hipLaunchKernelGGL((k_adj_pred<T, 2>), grid, block, 0, s, grids, items, nitems, U, A, dt0, ph);
+    hipLaunchKernelGGL((k_adj_pred<T, 2>), near, block, 0, s, grids, items, nitems, U, A, dt0, ph);
     hipLaunchKernelGGL((k_adj_face<T, 2>), dim3(nitems, 2), block, 0, s, grids, items, nitems, U, Lp, A, dt0, ph);
     hipLaunchKernelGGL((k_adj_cell<T, 2>), grid, block, 0, s, grids, items, nitems, U, A, dt0, ph);
-    hipLaunchKernelGGL((k_adj_prim<T, 2>), grid, block, 0, s, grids, items, nitems, U, A, ph);
-    hipLaunchKernelGGL((k_adj_assemble<T, 2>), grid, block, 0, s, grids, items, nitems, Lp, A, Lout);
+    hipLaunchKernelGGL((k_adj_prim<T, 2>), near, block, 0, s, grids, items, nitems, U, A, ph);
+    hipLaunchKernelGGL((k_adj_assemble<T, 2>), near, block, 0, s, grids, items, nitems, Lp, A, Lout);
     if (ninv > 0)
       hipLaunchKernelGGL((k_adj_fold<T, 2>), dim3(blocks_for(ninv), 6), block, 0, s, inv, ninv, dsts, A, Lout);
   }
