@@ -415,6 +415,13 @@ amr_status amr_get_error_flags(amr_hierarchy* h, uint32_t* flags, int64_t* first
  * forward-mode dual number.  `which` out of range or ntrials < 1 returns -1. */
 double amr_selfcheck_adjoint(int32_t which, int32_t ntrials, uint64_t seed);
 
+/* The advance's HLLD flux evaluated on the host (no GPU needed) in FP32
+ * (elem_bytes 4) or FP64 (8).  states: 17 values for each of the n Riemann
+ * problems, the left and the right primitive state (rho, u_n, u_t1, u_t2, p,
+ * unused, B_t1, B_t2) and the normal field B_n they share; flux: 7 values
+ * each (rho, m_n, m_t1, m_t2, E, B_t1, B_t2).  AMR_EINVAL for a bad argument. */
+int32_t amr_selfcheck_hlld(int32_t elem_bytes, int64_t n, const double* states, double gamma, double* flux);
+
 /* Host-only check of the advance kernels' addressing (no GPU needed): builds
  * the hierarchy's tables as amr_validate() does and, for every work list and
  * an element size of elem_bytes (4, 8 or 16), walks the work items as the

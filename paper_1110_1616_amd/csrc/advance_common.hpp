@@ -242,7 +242,7 @@ __device__ __forceinline__ bool hancock_states(const T (&w)[8], const T (&sl)[3]
   bool ok = true;
 #pragma unroll
   for (int d = 0; d < NDIM; ++d) {
-    T us[2][8], ir[2], q7[2][7];
+    T us[2][8], q7[2][7];
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
       T ws[8];
@@ -254,11 +254,10 @@ __device__ __forceinline__ bool hancock_states(const T (&w)[8], const T (&sl)[3]
 #pragma unroll
       for (int q = 0; q < 8; ++q) us[side][q] += du[q];
     }
-    drcp2(us[0][0], us[1][0], ir[0], ir[1]);
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
       T wb[8];
-      to_primitive_ir(us[side], wb, gm1, ir[side]);
+      to_primitive(us[side], wb, gm1);
       ok = ok && (wb[0] > T(0)) && (wb[4] > T(0));
       if (d == 0) rotate7<0>(wb, q7[side]);
       else if (d == 1) rotate7<1>(wb, q7[side]);

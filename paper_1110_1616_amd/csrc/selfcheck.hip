@@ -63,6 +63,19 @@ void rand_prim(Rng& r, double (&w)[8]) {
   w[7] = 0.6 * r.n();
 }
 
+// n Riemann problems (see amr.h) in precision S, widened to double.
+template <class S> void host_hlld(int64_t n, const double* x, double gamma, double* f) {
+  for (int64_t t = 0; t < n; ++t, x += 17, f += 7) {
+    S ql[8], qr[8], o[7];
+    for (int q = 0; q < 8; ++q) {
+      ql[q] = (S)x[q];
+      qr[q] = (S)x[8 + q];
+    }
+    riemann_hlld(ql, qr, (S)x[16], (S)gamma, S(1) / ((S)gamma - S(1)), o);
+    for (int q = 0; q < 7; ++q) f[q] = (double)o[q];
+  }
+}
+
 double rel(double a, double b) { return std::fabs(a - b) / (std::fabs(a) + std::fabs(b) + 1e-300); }
 
 }  // namespace
@@ -212,6 +225,13 @@ double amr_selfcheck_adjoint(int32_t which, int32_t ntrials, uint64_t seed) {
     if (e > worst) worst = e;
   }
   return worst;
+}
+
+int32_t amr_selfcheck_hlld(int32_t elem_bytes, int64_t n, const double* states, double gamma, double* flux) {
+  if ((elem_bytes != 4 && elem_bytes != 8) || n < 1 || !states || !flux || !(gamma > 1.0)) return AMR_EINVAL;
+  if (elem_bytes == 8) host_hlld<double>(n, states, gamma, flux);
+  else host_hlld<float>(n, states, gamma, flux);
+  return AMR_OK;
 }
 
 }  // extern "C"
