@@ -240,6 +240,9 @@ template <class T> __host__ __device__ __forceinline__ T fast_speed2(T r, T p, T
 // flux of every region is the physical flux of its state, evaluated once: the
 // inner (double-star) or star state of the chosen side by selects (waves hold
 // lanes of both), the outer state under a branch that subsonic flow skips.
+// The kept tangential field of a degenerate star state is the one that does
+// not satisfy them: its flux is put right by B_t (u - S_M), under a branch at
+// the end (summed where the states are selected it spilled 30 registers).
 // Against forming every state's jump F + S (U* - U) + S* (U** - U*) with
 // selects between both sides this is about 260 instead of 430 vector
 // instructions in double (a select of a double is two), and the kernels here
@@ -277,13 +280,14 @@ __host__ __device__ __forceinline__ void riemann_hlld(const T (&ql)[8], const T 
   // reciprocal in double: their product, rho (S - u) (S - S_M)^2, has the scale
   // of the energy flux, which has to be in range itself.
   T rsl, vsl, wsl, bysl, bzsl, vbsl, esl;
+  bool degl, degr;
   {
     const T dsm = sl - sm;
     const T den = rdl * dsm - bn2;
-    const bool deg = dabs(den) <= tiny;
+    degl = dabs(den) <= tiny;
     T idsm, iden;
-    drcp2(dsm, deg ? T(1) : den, idsm, iden);
-    const T g = deg ? T(0) : tl * iden;
+    drcp2(dsm, degl ? T(1) : den, idsm, iden);
+    const T g = degl ? T(0) : tl * iden;
     rsl = rdl * idsm;
     const T fv = bn * g, fb = T(1) + rdl * g;
     vsl = ql[2] - ql[6] * fv;
@@ -299,10 +303,10 @@ __host__ __device__ __forceinline__ void riemann_hlld(const T (&ql)[8], const T 
   {
     const T dsm = sr - sm;
     const T den = rdr * dsm - bn2;
-    const bool deg = dabs(den) <= tiny;
+    degr = dabs(den) <= tiny;
     T idsm, iden;
-    drcp2(dsm, deg ? T(1) : den, idsm, iden);
-    const T g = deg ? T(0) : tr * iden;
+    drcp2(dsm, degr ? T(1) : den, idsm, iden);
+    const T g = degr ? T(0) : tr * iden;
     rsr = rdr * idsm;
     const T fv = bn * g, fb = T(1) + rdr * g;
     vsr = qr[2] - qr[6] * fv;
@@ -343,7 +347,8 @@ __host__ __device__ __forceinline__ void riemann_hlld(const T (&ql)[8], const T 
   T w = inner ? wss : (left ? wsl : wsr);
   T by = inner ? byss : (left ? bysl : bysr);
   T bz = inner ? bzss : (left ? bzsl : bzsr);
-  if (left ? sl > T(0) : !(ssr >= T(0)) && !(sr >= T(0))) {  // beyond the fast waves: the outer state
+  const bool outer = left ? sl > T(0) : !(ssr >= T(0)) && !(sr >= T(0));
+  if (outer) {  // beyond the fast waves: the outer state
     r = left ? ql[0] : qr[0];
     u = left ? ql[1] : qr[1];
     v = left ? ql[2] : qr[2];
@@ -361,6 +366,11 @@ __host__ __device__ __forceinline__ void riemann_hlld(const T (&ql)[8], const T 
   f[4] = (e + pt) * u - bn * vb;
   f[5] = by * u - bn * v;
   f[6] = bz * u - bn * w;
+  if (!outer && (left ? degl : degr)) {  // the kept field crosses the outer wave with the outer state's flux
+    const T t = u - (left ? ql[1] : qr[1]);
+    f[5] -= (left ? ql[6] : qr[6]) * t;
+    f[6] -= (left ? ql[7] : qr[7]) * t;
+  }
 }
 
 }  // namespace amr
