@@ -268,12 +268,8 @@ __global__ __launch_bounds__(256) void k_update(const GridDesc* __restrict__ gri
         for (int s = 0; s < 5; ++s) {
           // lab conserved slot s -> rotated component of each direction
           const int qx = hydro_comp(s, 0), qy = hydro_comp(s, 1), qz = hydro_comp(s, 2);
-          const T xh = F.f[0][qx][e + 1], xl = F.f[0][qx][e], yh = F.f[1][qy][e + st[1]], yl = F.f[1][qy][e];
-          T acc;
-          if constexpr (NDIM == 3)
-            acc = add_high(flux_low(cdx, xh, xl, cdy, yh, yl, cdz, F.f[2][qz][e]), cdz, F.f[2][qz][e + st[2]]);
-          else
-            acc = flux_delta2(cdx, xh, xl, cdy, yh, yl);
+          T acc = flux_delta2(cdx, F.f[0][qx][e + 1], F.f[0][qx][e], cdy, F.f[1][qy][e + st[1]], F.f[1][qy][e]);
+          if constexpr (NDIM == 3) acc = add_delta(acc, cdz, F.f[2][qz][e + st[2]], F.f[2][qz][e]);
           Uout.f[s][e] = Uin.f[s][e] - acc;
         }
         if (NDIM == 2) {
@@ -287,12 +283,12 @@ __global__ __launch_bounds__(256) void k_update(const GridDesc* __restrict__ gri
         if (cy < uhy && k < uhz) {  // Bx face (cx, cy, k)
           T ez0 = emf_at<2, UPWIND>(F, e, st), ez1 = emf_at<2, UPWIND>(F, e + st[1], st);
           T ey0 = emf_at<1, UPWIND>(F, e, st), ey1 = emf_at<1, UPWIND>(F, e + st[2], st);
-          Uout.f[5][e] = Uin.f[5][e] - add_high(curl_low(cdy, ez1, ez0, cdz, ey0), -cdz, ey1);
+          Uout.f[5][e] = Uin.f[5][e] - curl_delta(cdy, ez1, ez0, cdz, ey1, ey0);
         }
         if (cx < uhx && k < uhz) {  // By face
           T ex0 = emf_at<0, UPWIND>(F, e, st), ex1 = emf_at<0, UPWIND>(F, e + st[2], st);
           T ez0 = emf_at<2, UPWIND>(F, e, st), ez1 = emf_at<2, UPWIND>(F, e + st[0], st);
-          Uout.f[6][e] = Uin.f[6][e] - add_high(curl_low(-cdx, ez1, ez0, -cdz, ex0), cdz, ex1);
+          Uout.f[6][e] = Uin.f[6][e] - curl_delta(cdz, ex1, ex0, cdx, ez1, ez0);
         }
         if (cx < uhx && cy < uhy) {  // Bz face
           T ey0 = emf_at<1, UPWIND>(F, e, st), ey1 = emf_at<1, UPWIND>(F, e + st[0], st);

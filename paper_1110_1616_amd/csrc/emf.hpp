@@ -18,32 +18,30 @@ template <class T> __device__ __forceinline__ T emf_mean(T b_lo, T b_hi, T c_lo,
   const T s2 = c_lo + c_hi;
   return T(0.25) * (s2 - s1);
 }
-// Flux difference of a cell field over its faces.  In 3-D in two parts, so
-// that a kernel marching along z carries one value a field between planes:
-// the terms of the x- and y-faces and of the low z-face,
-// cdx (F_x,high - F_x,low) + cdy (...) - cdz F_z,low, then the high z-face's.
-template <class T> __device__ __forceinline__ T flux_low(T cdx, T xh, T xl, T cdy, T yh, T yl, T cdz, T zl) {
-#pragma clang fp contract(off)
-  return cdx * (xh - xl) + cdy * (yh - yl) - cdz * zl;
-}
-template <class T> __device__ __forceinline__ T add_high(T low, T c, T high) {
-#pragma clang fp contract(off)
-  return low + c * high;
-}
+// Flux difference of a cell field over its faces: the terms of the x- and
+// y-faces, cdx (F_x,high - F_x,low) + cdy (...), then in 3-D + cdz (...).
 template <class T> __device__ __forceinline__ T flux_delta2(T cdx, T xh, T xl, T cdy, T yh, T yl) {
 #pragma clang fp contract(off)
   return cdx * (xh - xl) + cdy * (yh - yl);
 }
-// Curl term of a face update: c1 (a1 - a0) - c2 (b1 - b0); in 2-D the
-// single term c (a1 - a0).  With b along z again in two parts:
-// c1 (a1 - a0) + c2 b0, then add_high(., -c2, b1).
+template <class T> __device__ __forceinline__ T add_delta(T acc, T c, T high, T low) {
+#pragma clang fp contract(off)
+  return acc + c * (high - low);
+}
+// Curl term of a face update: c1 (a1 - a0) - c2 (b1 - b0), either term formed
+// before by a kernel that marches along z (t); in 2-D the single term
+// c (a1 - a0).
 template <class T> __device__ __forceinline__ T curl_delta(T c1, T a1, T a0, T c2, T b1, T b0) {
 #pragma clang fp contract(off)
   return c1 * (a1 - a0) - c2 * (b1 - b0);
 }
-template <class T> __device__ __forceinline__ T curl_low(T c1, T a1, T a0, T c2, T b0) {
+template <class T> __device__ __forceinline__ T minus_delta(T t, T c, T high, T low) {
 #pragma clang fp contract(off)
-  return c1 * (a1 - a0) + c2 * b0;
+  return t - c * (high - low);
+}
+template <class T> __device__ __forceinline__ T delta_minus(T c, T high, T low, T t) {
+#pragma clang fp contract(off)
+  return c * (high - low) - t;
 }
 template <class T> __device__ __forceinline__ T face_delta2(T c, T a1, T a0) {
 #pragma clang fp contract(off)

@@ -11,7 +11,7 @@
 // edge EMFs E_z of plane k and E_x, E_y at z = k - 1/2 of the lane and of its
 // neighbours, the update of plane k-1 (cells and their x- and y-faces) and
 // of the z-faces at k - 1/2.  What plane k's update needs of its own fluxes
-// is carried as one value a field.  A tile updates the cells of
+// is carried as two values a field.  A tile updates the cells of
 // lanes tx in [1, tw-2], ty in [1, th-2] (their high faces and the edges
 // around them are computed in the tile); tiles overlap by two columns and
 // rows (the last x- and y-face of the update region go to the lane that
@@ -25,7 +25,7 @@
 // 450 other instructions a wave in FP64; a wave alone on its SIMD issues at
 // most one of any kind every four cycles and waits for LDS, barriers and
 // dependent FP64 results in between, so two waves share each SIMD: 256
-// registers and 75 KB of LDS a block in FP64, two blocks a CU (150 registers
+// registers and 81 KB of LDS a block in FP64, two blocks a CU (159 registers
 // in FP32, three).  To fit, the z differences wait in LDS, W of the next
 // plane is read back from the W plane, and the loads of the next planes are
 // issued behind the Riemann problems instead of a plane ahead.  Against one
@@ -246,6 +246,10 @@ __global__ __launch_bounds__(256, (sizeof(T) == 8 ? 2 : 3)) void k_fused3(
   // F_x in 0..6, F_y in 7..13, the two EMF components of F_z in 14, 15
   __shared__ T sF[16][256];
   __shared__ T sD[8][256];  // W of the lane's cell minus the plane below
+  // What the update of the plane below needs next to `up` and fits no registers
+  // in FP64: F_x c6 and F_y c5 of its lanes and the lane's F_z of the density.
+  constexpr bool kPark = sizeof(T) == 8;
+  __shared__ T sP[kPark ? 3 : 1][kPark ? 256 : 1];
   __shared__ int s_claim[2], s_c;
   if (threadIdx.x == 0) s_c = 0;
 
@@ -327,10 +331,16 @@ __global__ __launch_bounds__(256, (sizeof(T) == 8 ? 2 : 3)) void k_fused3(
     T wnext[8], fb[3][2], zlo[7];  // W of plane k + 1; face fields of plane k; high z states of plane k - 1
 #pragma unroll
     for (int c = 0; c < 7; ++c) zlo[c] = T(1);
-    // carried from the plane below: the updates of its cells and x- and
-    // y-faces without the terms of the z-faces above them, and the EMF inputs
-    // F_y c5, F_x c6 of the lane, of its high x (F_x c6) and high y (F_y c5)
+    // carried from the plane below: the terms of the x- and y-faces in the
+    // updates of its cells, those of the E_z in its x- and y-faces', what the
+    // z-faces' and E_x, E_y above it are subtracted from (the hydro F_z, ey and
+    // ex), and the EMF inputs F_y c5, F_x c6 of the lane, of its high x (F_x c6)
+    // and high y (F_y c5).  (With the z terms' low parts subtracted at once it is
+    // one value a field and 128^3 takes 652 instead of 666 us, but c F_low and
+    // c F_high rounded apart do not cancel where they are equal: 3000 times the
+    // error in m_z of 1e-5 next to a pressure of 1 that does not depend on z.)
     T up[7] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
+    T zl[7] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
     T fy5p = T(0), fx6p = T(0), fx6r = T(0), fy5u = T(0);
     {
       // the item's first planes: every load issued before any conversion
@@ -346,6 +356,7 @@ __global__ __launch_bounds__(256, (sizeof(T) == 8 ? 2 : 3)) void k_fused3(
 #pragma unroll
       for (int c = 0; c < 8; ++c) {
         sD[c][tid] = w1[c] - w0[c];
+        if (kPark && c < 3) sP[c][tid] = T(0);
         if (ring && !rok) sW[c][rey * kW + rex] = T(1);
         sW[c][rw] = wring[c];
         sW[c][ew] = w1[c];
@@ -377,6 +388,10 @@ __global__ __launch_bounds__(256, (sizeof(T) == 8 ? 2 : 3)) void k_fused3(
           form_now(du);
         }
         __syncthreads();  // the plane below's fluxes have been read: the face states take their place
+        if constexpr (kPark) {  // (two free arrays until this plane's F_z)
+          sF[14][tid] = zl[1];
+          sF[15][tid] = zl[2];
+        }
         const bool ok = hancock_states<T, NDIM>(w, sl, du, fb, gm1, gm1_inv,
                                                 [&](int d, const T (&lo)[7], const T (&hi)[7]) {
 #pragma unroll
@@ -434,11 +449,23 @@ __global__ __launch_bounds__(256, (sizeof(T) == 8 ? 2 : 3)) void k_fused3(
       fb[1][1] = ldb(U.f[6], en + bx.sy);
       fb[2][0] = ldb(U.f[7], en);
       const unsigned mkn = fmask ? ldb(fmask, en / (unsigned)sizeof(T)) : 0u;
+      if constexpr (kPark) {
+        fx6p = sP[0][tid];
+        fx6r = sP[0][tr];
+        fy5p = sP[1][tid];
+        fy5u = sP[1][tu];
+        zl[1] = sF[14][tid];
+        zl[2] = sF[15][tid];
+      }
       __syncthreads();  // the face states have been read: the fluxes take their place
 #pragma unroll
       for (int c = 0; c < 7; ++c) {
         sF[c][tid] = fx[c];
         sF[7 + c][tid] = fy[c];
+      }
+      if constexpr (kPark) {
+        sP[0][tid] = fx[6];
+        sP[1][tid] = fy[5];
       }
       sF[14][tid] = fz[5];
       sF[15][tid] = fz[6];
@@ -466,19 +493,24 @@ __global__ __launch_bounds__(256, (sizeof(T) == 8 ? 2 : 3)) void k_fused3(
       fx6p = fx[6];
       fx6r = fx6n;
       fy5u = fy5n;
+      if constexpr (kPark) zl[0] = sP[2][tid];
       T un[8];
       un[7] = bn[2] - curl_delta(cdx, ey1, ey, cdy, ex1, ex);
 #pragma unroll
       for (int s = 0; s < 5; ++s) {
         const int qx = hydro_comp(s, 0), qy = hydro_comp(s, 1), qz = hydro_comp(s, 2);
-        un[s] = uo[s] - add_high(up[s], cdz, fz[qz]);
+        un[s] = uo[s] - add_delta(up[s], cdz, fz[qz], zl[s]);
         // plane k's, up to the z-faces above it
-        up[s] = flux_low<T>(cdx, sF[qx][tr], fx[qx], cdy, sF[7 + qy][tu], fy[qy], cdz, fz[qz]);
+        up[s] = flux_delta2<T>(cdx, sF[qx][tr], fx[qx], cdy, sF[7 + qy][tu], fy[qy]);
+        zl[s] = fz[qz];
       }
-      un[5] = uo[5] - add_high(up[5], -cdz, ey);
-      un[6] = uo[6] - add_high(up[6], cdz, ex);
-      up[5] = curl_low(cdy, ezy, ez0, cdz, ey);
-      up[6] = curl_low(-cdx, ezx, ez0, -cdz, ex);
+      if constexpr (kPark) sP[2][tid] = zl[0];
+      un[5] = uo[5] - minus_delta(up[5], cdz, ey, zl[5]);
+      un[6] = uo[6] - delta_minus(cdz, ex, zl[6], up[6]);
+      up[5] = face_delta2(cdy, ezy, ez0);
+      up[6] = face_delta2(cdx, ezx, ez0);
+      zl[5] = ey;
+      zl[6] = ex;
       fb[2][1] = rfb[2][0];
       raw3_to_prim<T>(rnext, rfb, gm1, wnext);
       form_now(wnext);
