@@ -421,6 +421,13 @@ double amr_selfcheck_adjoint(int32_t which, int32_t ntrials, uint64_t seed);
  * unused, B_t1, B_t2) and the normal field B_n they share; flux: 7 values
  * each (rho, m_n, m_t1, m_t2, E, B_t1, B_t2).  AMR_EINVAL for a bad argument. */
 int32_t amr_selfcheck_hlld(int32_t elem_bytes, int64_t n, const double* states, double gamma, double* flux);
+/* Host-only dot-product test of that flux's reverse on given states: for each
+ * problem forward <- <a, J d> by a forward-mode dual number and reverse <-
+ * <J^T a, d> by the hand-written reverse, with d (dstates, 17 values a problem)
+ * and a (aflux, 7).  Branches are those of the state itself in both.
+ * AMR_EINVAL for a bad argument. */
+int32_t amr_selfcheck_hlld_adjoint(int64_t n, const double* states, const double* dstates, const double* aflux,
+                                   double gamma, double* forward, double* reverse);
 
 /* Host-only check of the advance kernels' addressing (no GPU needed): builds
  * the hierarchy's tables as amr_validate() does and, for every work list and

@@ -2,7 +2,8 @@
 // written by hand from the forward code in mhd_device.hpp.  Each function
 // re-evaluates its forward pass, then propagates output adjoints back to its
 // inputs with every branch (min/max choices, clamps, HLLD region and
-// degeneracy tests, sign of B_n) frozen at the forward values.  Adjoints are
+// degeneracy tests, sign of B_n) frozen at the forward values (those of HLLD by
+// the routine that the flux calls).  Adjoints are
 // accumulated (+=) into the caller's input-adjoint arrays.
 #pragma once
 #include "mhd_device.hpp"
@@ -136,52 +137,42 @@ __host__ __device__ __forceinline__ void flux_along_adj(const T (&w)[8], T gm1_i
 template <class T>
 __host__ __device__ void riemann_hlld_adj(const T (&ql)[8], const T (&qr)[8], T bn, T gam, const T (&a_f)[7],
                                           T (&a_ql)[8], T (&a_qr)[8], T& a_bn) {
-  // ---------------- forward (same arithmetic as riemann_hlld) ----------------
+  // ---------------- forward ----------------
+  // waves, star densities and choices by riemann_hlld's own routine; the star
+  // states and fluxes as jumps F + S (U* - U) + S* (U** - U*), the same function
+  HlldFan<T> fan;
+  hlld_fan(ql, qr, bn, gam, fan);
   const T g1i = drcp(gam - T(1));
-  const T bn2 = bn * bn;
+  const T bn2 = fan.bn2;
   const T rl = ql[0], ul = ql[1], vl = ql[2], wl = ql[3], pl = ql[4], byl = ql[6], bzl = ql[7];
   const T rr = qr[0], ur = qr[1], vr = qr[2], wr = qr[3], pr = qr[4], byr = qr[6], bzr = qr[7];
-  const T b2l = bn2 + byl * byl + bzl * bzl;
-  const T b2r = bn2 + byr * byr + bzr * bzr;
-  const T ptl = pl + T(0.5) * b2l;
-  const T ptr = pr + T(0.5) * b2r;
+  const T b2l = fan.l.b2, b2r = fan.r.b2, ptl = fan.l.pt, ptr = fan.r.pt;
   const T kl = ul * ul + vl * vl + wl * wl;
   const T kr = ur * ur + vr * vr + wr * wr;
   const T el = pl * g1i + T(0.5) * rl * kl + T(0.5) * b2l;
   const T er = pr * g1i + T(0.5) * rr * kr + T(0.5) * b2r;
-  const T cfl = fast_magnetosonic(rl, pl, b2l, bn, gam);
-  const T cfr = fast_magnetosonic(rr, pr, b2r, bn, gam);
-  const bool cl_big = cfl > cfr;
-  const T cmx = cl_big ? cfl : cfr;
-  const bool ul_lt = ul < ur;
+  const bool ul_lt = ul < ur;  // the side of the smaller and of the larger u; of equal ones the right, as there
   const bool ul_gt = ul > ur;
-  const T sl = (ul_lt ? ul : ur) - cmx;
-  const T sr = (ul_gt ? ul : ur) + cmx;
-  const T dl = sl - ul, dr = sr - ur;
-  const T rdl = rl * dl, rdr = rr * dr;
-  const T num = rdr * ur - rdl * ul - ptr + ptl;
-  const T den = rdr - rdl;
-  const T sm = num * drcp(den);
-  const T pts = ptl + rdl * (sm - ul);
-  const T tiny = T(1e-12) * pts;
+  const T sl = fan.l.s, sr = fan.r.s, dl = fan.l.d, dr = fan.r.d, rdl = fan.l.rd, rdr = fan.r.rd;
+  const T den = rdr - rdl, sm = fan.sm, pts = fan.pts;
 
   struct Side {
-    T d, rd, dsm, idsm, rs, dn, idn, smu, fv, qq, fb, vs, ws, bys, bzs, vb, vbs, x, es;
+    T d, rd, dsm, idsm, rs, idn, smu, fv, qq, fb, vs, ws, bys, bzs, vb, vbs, x, es;
     bool deg;
   };
-  auto star = [&](T r, T u, T v, T w, T by, T bz, T e, T pt, T s, T rd) {
+  auto star = [&](const HlldSide<T>& h, T u, T v, T w, T by, T bz, T e) {
     Side o;
-    o.d = s - u;
-    o.rd = rd;
-    o.dsm = s - sm;
-    o.idsm = drcp(o.dsm);
-    o.rs = rd * o.idsm;
-    o.dn = rd * o.dsm - bn2;
-    o.deg = dabs(o.dn) <= tiny;
-    o.idn = o.deg ? T(0) : drcp(o.dn);
+    const T pt = h.pt;
+    o.d = h.d;
+    o.rd = h.rd;
+    o.dsm = h.s - sm;
+    o.idsm = h.idsm;
+    o.rs = h.rs;
+    o.deg = h.deg;
+    o.idn = o.deg ? T(0) : h.iden;
     o.smu = sm - u;
     o.fv = bn * o.smu * o.idn;
-    o.qq = rd * o.d - bn2;
+    o.qq = o.rd * o.d - bn2;
     o.fb = o.qq * o.idn;
     o.vs = o.deg ? v : v - by * o.fv;
     o.ws = o.deg ? w : w - bz * o.fv;
@@ -191,17 +182,15 @@ __host__ __device__ void riemann_hlld_adj(const T (&ql)[8], const T (&qr)[8], T 
     o.vbs = sm * bn + o.vs * o.bys + o.ws * o.bzs;
     o.x = o.d * e - pt * u + pts * sm + bn * (o.vb - o.vbs);
     o.es = o.x * o.idsm;
-    (void)r;
     return o;
   };
-  const Side L = star(rl, ul, vl, wl, byl, bzl, el, ptl, sl, rdl);
-  const Side R = star(rr, ur, vr, wr, byr, bzr, er, ptr, sr, rdr);
-  const T sql = psqrt(L.rs), sqr = psqrt(R.rs);
+  const Side L = star(fan.l, ul, vl, wl, byl, bzl, el);
+  const Side R = star(fan.r, ur, vr, wr, byr, bzr, er);
+  const T sql = fan.l.sq, sqr = fan.r.sq;
   const T sb = bn < T(0) ? T(-1) : T(1);  // d|bn|/dbn
   const T abn = dabs(bn);
-  const T ssl = sm - abn * drcp(sql);
-  const T ssr = sm + abn * drcp(sqr);
-  const bool ddeg = T(0.5) * bn2 <= tiny;
+  const T ssl = fan.l.sa, ssr = fan.r.sa;
+  const bool ddeg = fan.ddeg;
   const T sg = bn > T(0) ? T(1) : T(-1);
   const T isum = drcp(sql + sqr);
   const T nv = sql * L.vs + sqr * R.vs + (R.bys - L.bys) * sg;
@@ -211,14 +200,8 @@ __host__ __device__ void riemann_hlld_adj(const T (&ql)[8], const T (&qr)[8], T 
   const T vss = nv * isum, wss = nw * isum, byss = nby * isum, bzss = nbz * isum;
   const T vbss = sm * bn + vss * byss + wss * bzss;
   // essl = esl - sql (vbsl - vbss) sg ; essr = esr + sqr (vbsr - vbss) sg
-  int region;
-  if (sl > T(0)) region = 0;
-  else if (ssl >= T(0)) region = 1;
-  else if (sm >= T(0)) region = 2;
-  else if (ssr >= T(0)) region = 3;
-  else if (sr >= T(0)) region = 4;
-  else region = 5;
-  const bool left = region <= 2;
+  const bool left = fan.left;
+  const int region = left ? (fan.outer ? 0 : ssl >= T(0) ? 1 : 2) : (ssr >= T(0) ? 3 : fan.outer ? 5 : 4);
 
   // ---------------- reverse ----------------
   // adjoints of shared intermediates
@@ -558,7 +541,7 @@ __host__ __device__ void riemann_hlld_adj(const T (&ql)[8], const T (&qr)[8], T 
   else aRq[1] += a_sr;
   const T a_cmx = -a_sl + a_sr;
   T a_b2l = T(0), a_b2r = T(0);
-  if (cl_big)
+  if (fan.lfast)
     fast_magnetosonic_adj(rl, pl, b2l, bn, gam, a_cmx, aLq[0], aLq[4], a_b2l, a_bnl);
   else
     fast_magnetosonic_adj(rr, pr, b2r, bn, gam, a_cmx, aRq[0], aRq[4], a_b2r, a_bnl);

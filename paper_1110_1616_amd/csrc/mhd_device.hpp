@@ -231,6 +231,70 @@ template <class T> __host__ __device__ __forceinline__ T fast_speed2(T r, T p, T
   return T(0.5) * (a + root0(a * a - T(4) * cs2 * (bn2 * ir)));
 }
 
+// The waves of an HLLD fan and every choice its flux and the reverse of it make:
+// one side's wave speed S, star density and Alfven wave, and the region that
+// holds x/t = 0.  The reverse calls the same routine, so it follows the branch
+// the flux took also where the sides are equal to a few roundings.
+template <class T> struct HlldSide {
+  T b2, pt;       // |B|^2, total pressure
+  T s, d, rd;     // S, S - u, rho (S - u)
+  T idsm, iden;   // 1 / (S - S_M); 1 / (rho (S - u)(S - S_M) - bn^2), any where degenerate
+  T rs, sq, isq;  // star density, its root and reciprocal root
+  T sa;           // speed of the Alfven wave
+  bool deg;
+};
+template <class T> struct HlldFan {
+  HlldSide<T> l, r;
+  T bn2, sm, pts;
+  bool lfast;  // the left fast speed bounds the fan
+  bool left, inner, outer, ddeg;
+};
+template <class T>
+__host__ __device__ __forceinline__ void hlld_side(const T (&q)[8], T bn2, T sm, T tiny, HlldSide<T>& o) {
+  const T dsm = o.s - sm;
+  const T den = o.rd * dsm - bn2;
+  o.deg = dabs(den) <= tiny;
+  // both denominators from one reciprocal in double: their product,
+  // rho (S - u)(S - S_M)^2, has the scale of the energy flux, which has to be
+  // in range itself
+  drcp2(dsm, o.deg ? T(1) : den, o.idsm, o.iden);
+  o.rs = o.rd * o.idsm;
+  sqrt_rsqrt(o.rs, o.sq, o.isq);
+}
+template <class T>
+__host__ __device__ __forceinline__ void hlld_fan(const T (&ql)[8], const T (&qr)[8], T bn, T gam, HlldFan<T>& w) {
+  const T bn2 = w.bn2 = bn * bn;
+  w.l.b2 = bn2 + ql[6] * ql[6] + ql[7] * ql[7];
+  w.r.b2 = bn2 + qr[6] * qr[6] + qr[7] * qr[7];
+  w.l.pt = ql[4] + T(0.5) * w.l.b2;
+  w.r.pt = qr[4] + T(0.5) * w.r.b2;
+  // larger fast speed: the sides' c^2 are compared before the root
+  const T c2l = fast_speed2(ql[0], ql[4], w.l.b2, bn2, gam), c2r = fast_speed2(qr[0], qr[4], w.r.b2, bn2, gam);
+  w.lfast = c2l > c2r;
+  const T cmx = root0(pmax(c2r, c2l));
+  w.l.s = pmin(qr[1], ql[1]) - cmx;
+  w.r.s = pmax(qr[1], ql[1]) + cmx;
+  // contact speed and star total pressure
+  w.l.d = w.l.s - ql[1];
+  w.r.d = w.r.s - qr[1];
+  w.l.rd = ql[0] * w.l.d;
+  w.r.rd = qr[0] * w.r.d;
+  w.sm = (w.r.rd * qr[1] - w.l.rd * ql[1] - w.r.pt + w.l.pt) * drcp(w.r.rd - w.l.rd);
+  w.pts = w.l.pt + w.l.rd * (w.sm - ql[1]);
+  const T tiny = T(1e-12) * w.pts;
+  hlld_side(ql, bn2, w.sm, tiny, w.l);
+  hlld_side(qr, bn2, w.sm, tiny, w.r);
+  const T abn = dabs(bn);
+  w.l.sa = w.sm - abn * w.l.isq;
+  w.r.sa = w.sm + abn * w.r.isq;
+  w.ddeg = T(0.5) * bn2 <= tiny;
+  w.left = w.sm >= T(0) || w.l.s > T(0);
+  w.outer = w.left ? w.l.s > T(0) : !(w.r.sa >= T(0)) && !(w.r.s >= T(0));
+  // the inner state holds x/t = 0 unless a test before it does or the normal
+  // field is degenerate (the inner states then equal the star states)
+  w.inner = (w.left ? !(w.l.sa >= T(0)) : w.r.sa >= T(0)) && !w.ddeg;
+}
+
 // HLLD flux (Miyoshi & Kusano 2005).  Inputs in the rotated frame:
 // q = (rho, un, ut1, ut2, p, [unused], bt1, bt2); bn shared.  Output
 // f = (rho, m_n, m_t1, m_t2, E, B_t1, B_t2).  The region that contains
@@ -250,95 +314,55 @@ template <class T> __host__ __device__ __forceinline__ T fast_speed2(T r, T p, T
 template <class T>
 __host__ __device__ __forceinline__ void riemann_hlld(const T (&ql)[8], const T (&qr)[8], T bn, T gam, T gm1_inv,
                                                       T (&f)[7]) {
-  const T bn2 = bn * bn;
+  HlldFan<T> fan;
+  hlld_fan(ql, qr, bn, gam, fan);
+  const T bn2 = fan.bn2, sm = fan.sm, pts = fan.pts;
+  const bool left = fan.left, inner = fan.inner;
 
-  // Left / right totals.
-  const T b2l = bn2 + ql[6] * ql[6] + ql[7] * ql[7];
-  const T b2r = bn2 + qr[6] * qr[6] + qr[7] * qr[7];
-  const T ptl = ql[4] + T(0.5) * b2l;
-  const T ptr = qr[4] + T(0.5) * b2r;
-
-  // Larger fast speed: the sides' c^2 are compared before the root.
-  const T cmx = root0(pmax(fast_speed2(ql[0], ql[4], b2l, bn2, gam), fast_speed2(qr[0], qr[4], b2r, bn2, gam)));
-  const T sl = pmin(ql[1], qr[1]) - cmx;
-  const T sr = pmax(ql[1], qr[1]) + cmx;
-
-  // Contact speed and star total pressure.
-  const T dl = sl - ql[1];
-  const T dr = sr - qr[1];
-  const T rdl = ql[0] * dl;
-  const T rdr = qr[0] * dr;
-  const T sm = (rdr * qr[1] - rdl * ql[1] - ptr + ptl) * drcp(rdr - rdl);
-  const T tl = sm - ql[1], tr = sm - qr[1];
-  const T pts = ptl + rdl * tl;
-  const T tiny = T(1e-12) * pts;
-
-  // Outer star states: density, tangential v and B, energy.  With
+  // Outer star states: tangential v and B, energy.  With
   // g = (S_M - u) / (rho (S - u)(S - S_M) - bn^2) the tangential fields are
   // v* = v - bt bn g and bt* = bt (1 + rho (S - u) g); g = 0 (v and bt kept)
-  // where that denominator is degenerate.  Both denominators come from one
-  // reciprocal in double: their product, rho (S - u) (S - S_M)^2, has the scale
-  // of the energy flux, which has to be in range itself.
-  T rsl, vsl, wsl, bysl, bzsl, vbsl, esl;
-  bool degl, degr;
+  // where that denominator is degenerate.
+  T vsl, wsl, bysl, bzsl, vbsl, esl;
   {
-    const T dsm = sl - sm;
-    const T den = rdl * dsm - bn2;
-    degl = dabs(den) <= tiny;
-    T idsm, iden;
-    drcp2(dsm, degl ? T(1) : den, idsm, iden);
-    const T g = degl ? T(0) : tl * iden;
-    rsl = rdl * idsm;
-    const T fv = bn * g, fb = T(1) + rdl * g;
+    const HlldSide<T>& o = fan.l;
+    const T g = o.deg ? T(0) : (sm - ql[1]) * o.iden;
+    const T fv = bn * g, fb = T(1) + o.rd * g;
     vsl = ql[2] - ql[6] * fv;
     wsl = ql[3] - ql[7] * fv;
     bysl = ql[6] * fb;
     bzsl = ql[7] * fb;
     const T vb = ql[1] * bn + ql[2] * ql[6] + ql[3] * ql[7];
     vbsl = sm * bn + vsl * bysl + wsl * bzsl;
-    const T e = ql[4] * gm1_inv + T(0.5) * (ql[0] * (ql[1] * ql[1] + ql[2] * ql[2] + ql[3] * ql[3]) + b2l);
-    esl = (dl * e - ptl * ql[1] + pts * sm + bn * (vb - vbsl)) * idsm;
+    const T e = ql[4] * gm1_inv + T(0.5) * (ql[0] * (ql[1] * ql[1] + ql[2] * ql[2] + ql[3] * ql[3]) + o.b2);
+    esl = (o.d * e - o.pt * ql[1] + pts * sm + bn * (vb - vbsl)) * o.idsm;
   }
-  T rsr, vsr, wsr, bysr, bzsr, vbsr, esr;
+  T vsr, wsr, bysr, bzsr, vbsr, esr;
   {
-    const T dsm = sr - sm;
-    const T den = rdr * dsm - bn2;
-    degr = dabs(den) <= tiny;
-    T idsm, iden;
-    drcp2(dsm, degr ? T(1) : den, idsm, iden);
-    const T g = degr ? T(0) : tr * iden;
-    rsr = rdr * idsm;
-    const T fv = bn * g, fb = T(1) + rdr * g;
+    const HlldSide<T>& o = fan.r;
+    const T g = o.deg ? T(0) : (sm - qr[1]) * o.iden;
+    const T fv = bn * g, fb = T(1) + o.rd * g;
     vsr = qr[2] - qr[6] * fv;
     wsr = qr[3] - qr[7] * fv;
     bysr = qr[6] * fb;
     bzsr = qr[7] * fb;
     const T vb = qr[1] * bn + qr[2] * qr[6] + qr[3] * qr[7];
     vbsr = sm * bn + vsr * bysr + wsr * bzsr;
-    const T e = qr[4] * gm1_inv + T(0.5) * (qr[0] * (qr[1] * qr[1] + qr[2] * qr[2] + qr[3] * qr[3]) + b2r);
-    esr = (dr * e - ptr * qr[1] + pts * sm + bn * (vb - vbsr)) * idsm;
+    const T e = qr[4] * gm1_inv + T(0.5) * (qr[0] * (qr[1] * qr[1] + qr[2] * qr[2] + qr[3] * qr[3]) + o.b2);
+    esr = (o.d * e - o.pt * qr[1] + pts * sm + bn * (vb - vbsr)) * o.idsm;
   }
 
-  // Alfven speeds and the inner (double-star) state.
-  T sql, sqr, isql, isqr;
-  sqrt_rsqrt(rsl, sql, isql);
-  sqrt_rsqrt(rsr, sqr, isqr);
-  const T abn = dabs(bn);
-  const T ssl = sm - abn * isql;
-  const T ssr = sm + abn * isqr;
+  // The inner (double-star) state.
+  const T sql = fan.l.sq, sqr = fan.r.sq;
   const T sg = bn > T(0) ? T(1) : T(-1);
   const T isum = drcp(sql + sqr);
   const T ssg = sql * sqr * sg;
-  const bool left = sm >= T(0) || sl > T(0);
   const T vss = (sql * vsl + sqr * vsr + (bysr - bysl) * sg) * isum;
   const T wss = (sql * wsl + sqr * wsr + (bzsr - bzsl) * sg) * isum;
   const T byss = (sql * bysr + sqr * bysl + ssg * (vsr - vsl)) * isum;
   const T bzss = (sql * bzsr + sqr * bzsl + ssg * (wsr - wsl)) * isum;
   const T vbss = sm * bn + vss * byss + wss * bzss;
-  // The inner state holds x/t = 0 unless a test before it does or the normal
-  // field is degenerate (the inner states then equal the star states).
-  const bool inner = (left ? !(ssl >= T(0)) : ssr >= T(0)) && !(T(0.5) * bn2 <= tiny);
-  T r = left ? rsl : rsr, u = sm, pt = pts;
+  T r = left ? fan.l.rs : fan.r.rs, u = sm, pt = pts;
   T vb = left ? vbsl : vbsr;
   T e = left ? esl : esr;
   e = inner ? e - (left ? sql : -sqr) * sg * (vb - vbss) : e;
@@ -347,17 +371,16 @@ __host__ __device__ __forceinline__ void riemann_hlld(const T (&ql)[8], const T 
   T w = inner ? wss : (left ? wsl : wsr);
   T by = inner ? byss : (left ? bysl : bysr);
   T bz = inner ? bzss : (left ? bzsl : bzsr);
-  const bool outer = left ? sl > T(0) : !(ssr >= T(0)) && !(sr >= T(0));
-  if (outer) {  // beyond the fast waves: the outer state
+  if (fan.outer) {  // beyond the fast waves: the outer state
     r = left ? ql[0] : qr[0];
     u = left ? ql[1] : qr[1];
     v = left ? ql[2] : qr[2];
     w = left ? ql[3] : qr[3];
     by = left ? ql[6] : qr[6];
     bz = left ? ql[7] : qr[7];
-    pt = left ? ptl : ptr;
+    pt = left ? fan.l.pt : fan.r.pt;
     vb = u * bn + v * by + w * bz;
-    e = (left ? ql[4] : qr[4]) * gm1_inv + T(0.5) * (r * (u * u + v * v + w * w) + (left ? b2l : b2r));
+    e = (left ? ql[4] : qr[4]) * gm1_inv + T(0.5) * (r * (u * u + v * v + w * w) + (left ? fan.l.b2 : fan.r.b2));
   }
   f[0] = r * u;
   f[1] = f[0] * u + (pt - bn2);
@@ -366,7 +389,7 @@ __host__ __device__ __forceinline__ void riemann_hlld(const T (&ql)[8], const T 
   f[4] = (e + pt) * u - bn * vb;
   f[5] = by * u - bn * v;
   f[6] = bz * u - bn * w;
-  if (!outer && (left ? degl : degr)) {  // the kept field crosses the outer wave with the outer state's flux
+  if (!fan.outer && (left ? fan.l.deg : fan.r.deg)) {  // the kept field crosses the outer wave with the outer state's flux
     const T t = u - (left ? ql[1] : qr[1]);
     f[5] -= (left ? ql[6] : qr[6]) * t;
     f[6] -= (left ? ql[7] : qr[7]) * t;

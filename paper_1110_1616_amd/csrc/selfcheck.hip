@@ -34,6 +34,12 @@ __host__ __device__ inline bool operator<(HDual a, HDual b) { return a.v < b.v; 
 __host__ __device__ inline bool operator>(HDual a, HDual b) { return a.v > b.v; }
 __host__ __device__ inline bool operator<=(HDual a, HDual b) { return a.v <= b.v; }
 __host__ __device__ inline bool operator>=(HDual a, HDual b) { return a.v >= b.v; }
+// (found by its argument; the values as double forms them, so that both take the same branches)
+__host__ __device__ inline void drcp2(HDual a, HDual b, HDual& ia, HDual& ib) {
+  const HDual r = HDual(1.0) / (a * b);
+  ia = r * b;
+  ib = r * a;
+}
 namespace amr {
 template <> __host__ __device__ inline HDual dsqrt<HDual>(HDual x) {
   const double s = __builtin_sqrt(x.v);
@@ -231,6 +237,29 @@ int32_t amr_selfcheck_hlld(int32_t elem_bytes, int64_t n, const double* states, 
   if ((elem_bytes != 4 && elem_bytes != 8) || n < 1 || !states || !flux || !(gamma > 1.0)) return AMR_EINVAL;
   if (elem_bytes == 8) host_hlld<double>(n, states, gamma, flux);
   else host_hlld<float>(n, states, gamma, flux);
+  return AMR_OK;
+}
+
+int32_t amr_selfcheck_hlld_adjoint(int64_t n, const double* states, const double* dstates, const double* aflux,
+                                   double gamma, double* forward, double* reverse) {
+  if (n < 1 || !states || !dstates || !aflux || !forward || !reverse || !(gamma > 1.0)) return AMR_EINVAL;
+  for (int64_t t = 0; t < n; ++t) {
+    const double *x = states + 17 * t, *d = dstates + 17 * t, *a = aflux + 7 * t;
+    HDual ql[8], qr[8], f[7];
+    double pl[8], pr[8], af[7], al[8] = {0}, ar[8] = {0}, abn = 0.0;
+    for (int q = 0; q < 8; ++q) {
+      ql[q] = HDual(pl[q] = x[q], d[q]);
+      qr[q] = HDual(pr[q] = x[8 + q], d[8 + q]);
+    }
+    for (int q = 0; q < 7; ++q) af[q] = a[q];
+    riemann_hlld(ql, qr, HDual(x[16], d[16]), HDual(gamma), HDual(1.0 / (gamma - 1.0)), f);
+    riemann_hlld_adj(pl, pr, x[16], gamma, af, al, ar, abn);
+    forward[t] = 0.0;
+    reverse[t] = abn * d[16];
+    for (int q = 0; q < 7; ++q) forward[t] += a[q] * f[q].d;
+    for (int q = 0; q < 8; ++q)
+      if (q != 5) reverse[t] += al[q] * d[q] + ar[q] * d[8 + q];
+  }
   return AMR_OK;
 }
 
