@@ -352,9 +352,9 @@ amr_status amr_load_primitive_adjoint(amr_hierarchy* h, int32_t grid, const doub
  * expression, so an expression rounds the same way in every kernel).
  * Changing tile_policy, zchunk or the XCD chunking (bit 1: items are ordered
  * longest first inside each XCD's chunk, else over the whole list) rebuilds
- * the work lists and drops captured graphs.  Default: 1, 16, 0; until a
- * configuration is set (here or by amr_autotune()), the fused kernel runs
- * wherever it can, as with bit 3. */
+ * the work lists and drops captured graphs.  Default: 1, 16, 8 with the mean
+ * EMF, 1, 16, 0 with the upwinded one; amr_get_launch_config() gives it back
+ * until another is set. */
 amr_status amr_set_launch_config(amr_hierarchy* h, int32_t tile_policy, int32_t zchunk, int32_t launch_mode);
 amr_status amr_get_launch_config(const amr_hierarchy* h, int32_t* tile_policy, int32_t* zchunk, int32_t* launch_mode);
 

@@ -44,7 +44,7 @@ void run_list(amr_hierarchy* h, const LaunchList& L, const amr_state* Ua, const 
     HIPCHK(hipEventRecord(h->ev_pool[e0], s));
   }
   if constexpr (std::is_same<T, float>::value || std::is_same<T, double>::value) {
-    if ((h->fused || !h->configured) && !h->upwind_emf) {
+    if (h->fused && !h->upwind_emf) {
       // one fused flux-update launch; the update's event pair measures zero
       launch_fused<T>(h->ndim, h->d_desc, h->d_xitems + L.fused.off, L.fused.n, s0, s1, parity, F, h->d_fmask, dt0, ph,
                       h->d_err, h->d_queue, h->persistent_flux ? h->fused_pblocks : 0, h->xcd_chunks, h->claim, s);

@@ -118,13 +118,12 @@ struct amr_hierarchy {
   // normal to d (the fused kernel stores only those)
   std::vector<uint8_t> h_fmask;
   uint8_t* d_fmask = nullptr;
-  bool fused = false;  // launch mode bit 3: one fused flux-update kernel per launch
-  // A configuration was set.  Until then launches take the fused kernel: it
-  // gives the two kernels' results bit for bit, in less time on every size
-  // (two steps, one 2-D grid of 64^2 48 -> 42 us, of 1021 x 517 FP32 116 ->
-  // 80; 37 x 33 x 35 FP32 71 -> 65; coarse steps of small 2-D and 3-D
-  // hierarchies 257 -> 225 and 469 -> 460).
-  bool configured = false;
+  // Launch mode bit 3: one fused flux-update kernel per launch.  A new hierarchy
+  // has it set (with the mean EMF): it gives the two kernels' results bit for
+  // bit, in less time on every size (two steps of one 2-D grid of 64^2
+  // 44 -> 40 us, of 1021 x 517 FP32 116 -> 73; 37 x 33 x 35 FP32 71 -> 65; coarse
+  // steps of small 2-D and 3-D hierarchies 257 -> 218 and 469 -> 460).
+  bool fused = false;
   int fused_pblocks = 0;
   int4* d_cfl = nullptr;
   int n_cfl = 0;

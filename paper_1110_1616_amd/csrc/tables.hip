@@ -1245,6 +1245,7 @@ amr_hierarchy* build_hierarchy(const amr_params* p, const amr_grid* grids, int32
     // the advance kernels address the level arrays by 32-bit byte offsets
     if (off * h->esize >= ((int64_t)1 << 32)) throw Error(AMR_EUNSUPPORTED, "hierarchy exceeds 4 GiB per field");
     h->upwind_emf = p->emf == AMR_EMF_UPWIND;
+    h->fused = !h->upwind_emf;
     h->flux_bytes = (h->upwind_emf ? 27 : 21) * off * (int64_t)h->esize;
     h->reg_offset = (h->flux_bytes + 255) / 256 * 256;
     check_nesting(h);
@@ -1329,7 +1330,6 @@ void set_launch_config(amr_hierarchy* h, int policy, int zchunk, int mode) {
   h->persistent_flux = (mode & 5) != 0;
   const bool xcd = (mode & 2) != 0;
   h->fused = (mode & 8) != 0;
-  h->configured = true;
   // the item order depends on the XCD chunking (see make_list)
   if (policy != h->tile_policy || zchunk != h->zchunk || xcd != h->xcd_chunks) {
     h->tile_policy = policy;
