@@ -499,10 +499,14 @@ void build_fill_maps(amr_hierarchy* h) {
   h->n_pface.assign(h->nlev, 0);
 
   // Every (level, grid, class) is independent: worker threads build each one's
-  // entries into lists of its own, concatenated in grid order afterwards.  All
-  // levels go through one loop, a grid's classes apart, because level 0 is
-  // often a single grid, its largest (a tree of 48 grids on 48^3, 16 threads:
-  // 9.4 ms with a loop a level and a thread a grid, 7.0 ms so).
+  // entries into lists of its own, concatenated in grid order afterwards.  A
+  // grid's classes go apart, because level 0 is often a single grid, its largest,
+  // and so do the levels of one loop: consecutive ones, as many as have kGroup
+  // band elements together, so that not much more than one large level's lists
+  // are held at a time (a tree of 48 grids on 48^3, 16 threads: 9.4 ms with a
+  // loop a level and a thread a grid, 7.0 ms so; all levels of a 3593-grid tree
+  // in one loop hold 6.9 GB instead of 2.8).
+  constexpr int64_t kGroup = 1 << 22;
   struct ClassMaps {
     std::vector<CopyEntry> cp;
     std::vector<CopyEntry> cp2;  // the entries within 2 cells of the interior
@@ -510,12 +514,14 @@ void build_fill_maps(amr_hierarchy* h) {
     std::exception_ptr err;
   };
   std::vector<std::vector<ClassMaps>> per(h->nlev);  // per[l][4 slot + cls]
-  std::vector<std::pair<int, int>> units;            // (l, 4 slot + cls)
-  for (int l = 0; l < h->nlev; ++l) {
-    per[l].resize(4 * h->level_grids[l].size());
-    for (size_t g = 0; g < h->level_grids[l].size(); ++g)
-      for (int cls = 0; cls < ncls; ++cls) units.push_back({l, (int)(4 * g) + cls});
-  }
+  auto band_elems = [&](int l) {
+    int64_t n = 0;
+    for (int gi : h->level_grids[l]) {
+      const GridDesc& G = h->desc[gi];
+      n += (int64_t)ncls * ((int64_t)G.P[0] * G.P[1] * G.P[2] - (int64_t)G.n[0] * G.n[1] * G.n[2]);
+    }
+    return n;
+  };
   auto one_class = [&](int l, int slot, int cls) {
     const LevelIndex& LI = idx[l];
     const std::vector<int>& lg = h->level_grids[l];
@@ -664,77 +670,85 @@ void build_fill_maps(amr_hierarchy* h) {
       }
     }
   };
-  parallel_for(units.size(), [&](size_t u) {
-    const int l = units[u].first, slot = units[u].second / 4, cls = units[u].second % 4;
-    try {
-      one_class(l, slot, cls);
-    } catch (...) {
-      per[l][units[u].second].err = std::current_exception();
-    }
-  });
-  for (auto& level : per)
-    for (ClassMaps& m : level)
-      if (m.err) std::rethrow_exception(m.err);
-  // concatenate: copies class by class (cells, x-, y-, z-faces), each in
-  // grid order; prolongations in grid order, a grid's faces class by class.
-  // Every list goes to an offset known in advance, copied (and freed) by the
-  // worker threads.
   struct LevelMaps {
     std::vector<size_t> o1, o2, opc, opf;
     RawVec<CopyEntry> all, all2;
     RawVec<ProlongEntry> pc, pf;
   };
   std::vector<LevelMaps> maps(h->nlev);
-  for (int l = 0; l < h->nlev; ++l) {
-    const size_t ng = h->level_grids[l].size();
-    LevelMaps& M = maps[l];
-    M.o1.assign(4 * ng + 1, 0);
-    M.o2.assign(4 * ng + 1, 0);
-    M.opc.assign(ng + 1, 0);
-    M.opf.assign(3 * ng + 1, 0);
-    for (int c = 0; c < 4; ++c)
-      for (size_t g = 0; g < ng; ++g) {
-        M.o1[c * ng + g + 1] = M.o1[c * ng + g] + per[l][4 * g + c].cp.size();
-        M.o2[c * ng + g + 1] = M.o2[c * ng + g] + per[l][4 * g + c].cp2.size();
-      }
-    for (size_t g = 0; g < ng; ++g) {
-      M.opc[g + 1] = M.opc[g] + per[l][4 * g].pr.size();
-      for (int c = 1; c < 4; ++c) M.opf[3 * g + c] = M.opf[3 * g + c - 1] + per[l][4 * g + c].pr.size();
+  for (int l0 = 0, l1 = 0; l0 < h->nlev; l0 = l1) {
+    int64_t elems = band_elems(l0);
+    for (l1 = l0 + 1; l1 < h->nlev && elems + band_elems(l1) <= kGroup; ++l1) elems += band_elems(l1);
+    std::vector<std::pair<int, int>> units;  // (l, 4 slot + cls)
+    for (int l = l0; l < l1; ++l) {
+      per[l].resize(4 * h->level_grids[l].size());
+      for (size_t g = 0; g < h->level_grids[l].size(); ++g)
+        for (int cls = 0; cls < ncls; ++cls) units.push_back({l, (int)(4 * g) + cls});
     }
-    M.all = RawVec<CopyEntry>(M.o1[4 * ng]);
-    M.all2 = RawVec<CopyEntry>(M.o2[4 * ng]);
-    M.pc = RawVec<ProlongEntry>(M.opc[ng]);
-    M.pf = RawVec<ProlongEntry>(M.opf[3 * ng]);
-  }
-  parallel_for(units.size(), [&](size_t u) {
-    const int l = units[u].first, slot = units[u].second / 4, c = units[u].second % 4;
-    LevelMaps& M = maps[l];
-    ClassMaps& m = per[l][units[u].second];
-    const size_t at = c * h->level_grids[l].size() + slot;
-    std::copy(m.cp.begin(), m.cp.end(), M.all.begin() + M.o1[at]);
-    std::copy(m.cp2.begin(), m.cp2.end(), M.all2.begin() + M.o2[at]);
-    if (c == 0) std::copy(m.pr.begin(), m.pr.end(), M.pc.begin() + M.opc[slot]);
-    else std::copy(m.pr.begin(), m.pr.end(), M.pf.begin() + M.opf[3 * slot + c - 1]);
-    m = ClassMaps();
-  });
-  for (int l = 0; l < h->nlev; ++l) {
-    const size_t ng = h->level_grids[l].size();
-    const std::vector<size_t>&o1 = maps[l].o1, &o2 = maps[l].o2;
-    RawVec<CopyEntry>&all = maps[l].all, &all2 = maps[l].all2;
-    RawVec<ProlongEntry>&pc = maps[l].pc, &pf = maps[l].pf;
-    const int4 cls = make_int4((int)o1[ng], (int)o1[2 * ng], (int)o1[3 * ng], (int)o1[4 * ng]);
-    const int4 cls2 = make_int4((int)o2[ng], (int)o2[2 * ng], (int)o2[3 * ng], (int)o2[4 * ng]);
-    h->copy2_cls[l] = cls2;
-    h->n_copy2[l] = (int)all2.size();
-    h->d_copy2[l] = dev_upload(all2);
-    h->copy_cls[l] = cls;
-    h->n_copy[l] = (int)all.size();
-    h->d_copy[l] = dev_upload(all);
-    h->h_copy[l] = std::move(all);
-    h->n_pcell[l] = (int)pc.size();
-    h->n_pface[l] = (int)pf.size();
-    h->d_pcell[l] = dev_upload(pc);
-    h->d_pface[l] = dev_upload(pf);
+    parallel_for(units.size(), [&](size_t u) {
+      const int l = units[u].first, slot = units[u].second / 4, cls = units[u].second % 4;
+      try {
+        one_class(l, slot, cls);
+      } catch (...) {
+        per[l][units[u].second].err = std::current_exception();
+      }
+    });
+    for (int l = l0; l < l1; ++l)
+      for (ClassMaps& m : per[l])
+        if (m.err) std::rethrow_exception(m.err);
+    // concatenate: copies class by class (cells, x-, y-, z-faces), each in
+    // grid order; prolongations in grid order, a grid's faces class by class.
+    // Every list goes to an offset known in advance, copied (and freed) by the
+    // worker threads.
+    for (int l = l0; l < l1; ++l) {
+      const size_t ng = h->level_grids[l].size();
+      LevelMaps& M = maps[l];
+      M.o1.assign(4 * ng + 1, 0);
+      M.o2.assign(4 * ng + 1, 0);
+      M.opc.assign(ng + 1, 0);
+      M.opf.assign(3 * ng + 1, 0);
+      for (int c = 0; c < 4; ++c)
+        for (size_t g = 0; g < ng; ++g) {
+          M.o1[c * ng + g + 1] = M.o1[c * ng + g] + per[l][4 * g + c].cp.size();
+          M.o2[c * ng + g + 1] = M.o2[c * ng + g] + per[l][4 * g + c].cp2.size();
+        }
+      for (size_t g = 0; g < ng; ++g) {
+        M.opc[g + 1] = M.opc[g] + per[l][4 * g].pr.size();
+        for (int c = 1; c < 4; ++c) M.opf[3 * g + c] = M.opf[3 * g + c - 1] + per[l][4 * g + c].pr.size();
+      }
+      M.all = RawVec<CopyEntry>(M.o1[4 * ng]);
+      M.all2 = RawVec<CopyEntry>(M.o2[4 * ng]);
+      M.pc = RawVec<ProlongEntry>(M.opc[ng]);
+      M.pf = RawVec<ProlongEntry>(M.opf[3 * ng]);
+    }
+    parallel_for(units.size(), [&](size_t u) {
+      const int l = units[u].first, slot = units[u].second / 4, c = units[u].second % 4;
+      LevelMaps& M = maps[l];
+      ClassMaps& m = per[l][units[u].second];
+      const size_t at = c * h->level_grids[l].size() + slot;
+      std::copy(m.cp.begin(), m.cp.end(), M.all.begin() + M.o1[at]);
+      std::copy(m.cp2.begin(), m.cp2.end(), M.all2.begin() + M.o2[at]);
+      if (c == 0) std::copy(m.pr.begin(), m.pr.end(), M.pc.begin() + M.opc[slot]);
+      else std::copy(m.pr.begin(), m.pr.end(), M.pf.begin() + M.opf[3 * slot + c - 1]);
+      m = ClassMaps();
+    });
+    for (int l = l0; l < l1; ++l) {
+      const size_t ng = h->level_grids[l].size();
+      LevelMaps& M = maps[l];
+      h->copy_cls[l] = make_int4((int)M.o1[ng], (int)M.o1[2 * ng], (int)M.o1[3 * ng], (int)M.o1[4 * ng]);
+      h->copy2_cls[l] = make_int4((int)M.o2[ng], (int)M.o2[2 * ng], (int)M.o2[3 * ng], (int)M.o2[4 * ng]);
+      h->n_copy2[l] = (int)M.all2.size();
+      h->d_copy2[l] = dev_upload(M.all2);
+      h->n_copy[l] = (int)M.all.size();
+      h->d_copy[l] = dev_upload(M.all);
+      h->h_copy[l] = std::move(M.all);
+      h->n_pcell[l] = (int)M.pc.size();
+      h->n_pface[l] = (int)M.pf.size();
+      h->d_pcell[l] = dev_upload(M.pc);
+      h->d_pface[l] = dev_upload(M.pf);
+      M = LevelMaps();
+      std::vector<ClassMaps>().swap(per[l]);
+    }
   }
 }
 
@@ -1253,22 +1267,29 @@ amr_hierarchy* build_hierarchy(const amr_params* p, const amr_grid* grids, int32
     build_fill_maps(h);
     build_lists(h);
     h->sync.resize(h->nlev);
-    // the levels' entries on worker threads (level 1's coarse side is often a
-    // single grid: 6.2 ms one level after the other, 4.6 together); the
-    // device is this thread's, so the uploads stay here
+    // The levels' entries: on worker threads (level
+    // 1's coarse side is often a single grid: 6.2 ms one level after the other,
+    // 4.6 together on 48 grids over 48^3); of a large one level after level, each
+    // uploaded and freed before the next, so that one level's are held at a time.
+    // The device is this thread's, so the uploads stay here.
+    const bool together = h->total_elems <= (1 << 22);
     std::vector<SyncEntries> sync(h->nlev);
-    parallel_for((size_t)h->nlev - 1, [&](size_t t) {
-      try {
-        build_sync_entries(h, (int)t + 1, sync[t + 1]);
-      } catch (...) {
-        sync[t + 1].err = std::current_exception();
-      }
-    });
-    for (SyncEntries& e : sync)
-      if (e.err) std::rethrow_exception(e.err);
+    if (together) {
+      parallel_for((size_t)h->nlev - 1, [&](size_t t) {
+        try {
+          build_sync_entries(h, (int)t + 1, sync[t + 1]);
+        } catch (...) {
+          sync[t + 1].err = std::current_exception();
+        }
+      });
+      for (SyncEntries& e : sync)
+        if (e.err) std::rethrow_exception(e.err);
+    }
     int64_t reg_bytes = 0;
     for (int l = 1; l < h->nlev; ++l) {
+      if (!together) build_sync_entries(h, l, sync[l]);
       upload_sync_tables(h, l, sync[l]);
+      sync[l] = SyncEntries();
       h->sync[l].reg_off = h->reg_offset + reg_bytes;
       reg_bytes += (h->sync[l].reg_bytes + 255) / 256 * 256;
     }
