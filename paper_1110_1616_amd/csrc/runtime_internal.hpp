@@ -384,11 +384,17 @@ inline int64_t elem(const GridDesc& G, int ndim, int i, int j, int k) {
   return G.off + (int64_t)(i + G.g) + (int64_t)(j + G.g) * G.P[0] + (int64_t)(k + gz) * G.P[0] * G.P[1];
 }
 
-// Run fn(i) for i in [0, n) on up to hardware_concurrency() threads; the
-// first exception thrown by any call is rethrown here.
+// Run fn(i) for i in [0, n) on up to hardware_concurrency() threads, the
+// caller's among them; the first exception thrown by any call is rethrown here.
+// A loop inside another one's call takes that loop's share of the threads.
+inline unsigned& thread_share() {
+  thread_local unsigned share = 0;  // 0: not inside a loop
+  return share;
+}
 template <class Fn> inline void parallel_for(size_t n, Fn&& fn) {
   const unsigned hw = std::max(1u, std::min(32u, std::thread::hardware_concurrency()));
-  const unsigned nt = (unsigned)std::min<size_t>(hw, n);
+  const unsigned outer = thread_share(), avail = outer ? outer : hw;
+  const unsigned nt = (unsigned)std::min<size_t>(avail, n);
   if (nt <= 1) {
     for (size_t i = 0; i < n; ++i) fn(i);
     return;
@@ -396,24 +402,44 @@ template <class Fn> inline void parallel_for(size_t n, Fn&& fn) {
   std::atomic<size_t> next{0};
   std::exception_ptr err;
   std::mutex mu;
-  std::vector<std::thread> pool;
-  for (unsigned t = 0; t < nt; ++t)
-    pool.emplace_back([&]() {
-      for (;;) {
-        const size_t i = next.fetch_add(1);
-        if (i >= n) return;
-        try {
-          fn(i);
-        } catch (...) {
-          std::lock_guard<std::mutex> g(mu);
-          if (!err) err = std::current_exception();
-          next.store(n);
-          return;
-        }
+  auto work = [&]() {
+    for (;;) {
+      const size_t i = next.fetch_add(1);
+      if (i >= n) return;
+      try {
+        fn(i);
+      } catch (...) {
+        std::lock_guard<std::mutex> g(mu);
+        if (!err) err = std::current_exception();
+        next.store(n);
+        return;
       }
-    });
+    }
+  };
+  const unsigned share = std::max(1u, avail / nt);
+  std::vector<std::thread> pool;
+  pool.reserve(nt - 1);
+  try {
+    for (unsigned t = 1; t < nt; ++t)
+      pool.emplace_back([&, share]() {
+        thread_share() = share;
+        work();
+      });
+  } catch (const std::system_error&) {
+    // no more threads to be had: those there are do the work
+  }
+  thread_share() = share;
+  work();
+  thread_share() = outer;
   for (auto& th : pool) th.join();
   if (err) std::rethrow_exception(err);
+}
+// The same on the caller's thread alone where the loop's work is small:
+// starting and joining the threads takes 0.2 ms.
+template <class Fn> inline void parallel_for_if(bool large, size_t n, Fn&& fn) {
+  if (large) parallel_for(n, fn);
+  else
+    for (size_t i = 0; i < n; ++i) fn(i);
 }
 
 inline int64_t align256(int64_t x) { return (x + 255) / 256 * 256; }
@@ -454,7 +480,6 @@ bool own_elem(const GridDesc& G, int ndim, int cls, const int (&x)[3]);
 void class_extent(const GridDesc& G, int ndim, int cls, int (&lo)[3], int (&hi)[3]);
 void build_fill_maps(amr_hierarchy* h);
 void check_nesting(amr_hierarchy* h);
-void build_sync_tables(amr_hierarchy* h, int f);
 amr_hierarchy* build_hierarchy(const amr_params* p, const amr_grid* grids, int32_t ngrids);
 void rebuild_lists(amr_hierarchy* h);
 void set_update_zchunk(amr_hierarchy* h, int zchunk);

@@ -505,8 +505,8 @@ void build_fill_maps(amr_hierarchy* h) {
   // band elements together, so that not much more than one large level's lists
   // are held at a time (a tree of 48 grids on 48^3, 16 threads: 9.4 ms with a
   // loop a level and a thread a grid, 7.0 ms so; all levels of a 3593-grid tree
-  // in one loop hold 6.9 GB instead of 2.8).
-  constexpr int64_t kGroup = 1 << 22;
+  // in one loop hold 6.9 GB instead of 2.8).  Small levels stay on this thread.
+  constexpr int64_t kGroup = 1 << 22, kSmall = 1 << 13;
   struct ClassMaps {
     std::vector<CopyEntry> cp;
     std::vector<CopyEntry> cp2;  // the entries within 2 cells of the interior
@@ -679,13 +679,14 @@ void build_fill_maps(amr_hierarchy* h) {
   for (int l0 = 0, l1 = 0; l0 < h->nlev; l0 = l1) {
     int64_t elems = band_elems(l0);
     for (l1 = l0 + 1; l1 < h->nlev && elems + band_elems(l1) <= kGroup; ++l1) elems += band_elems(l1);
+    const bool large = elems > kSmall;
     std::vector<std::pair<int, int>> units;  // (l, 4 slot + cls)
     for (int l = l0; l < l1; ++l) {
       per[l].resize(4 * h->level_grids[l].size());
       for (size_t g = 0; g < h->level_grids[l].size(); ++g)
         for (int cls = 0; cls < ncls; ++cls) units.push_back({l, (int)(4 * g) + cls});
     }
-    parallel_for(units.size(), [&](size_t u) {
+    parallel_for_if(large, units.size(), [&](size_t u) {
       const int l = units[u].first, slot = units[u].second / 4, cls = units[u].second % 4;
       try {
         one_class(l, slot, cls);
@@ -721,7 +722,7 @@ void build_fill_maps(amr_hierarchy* h) {
       M.pc = RawVec<ProlongEntry>(M.opc[ng]);
       M.pf = RawVec<ProlongEntry>(M.opf[3 * ng]);
     }
-    parallel_for(units.size(), [&](size_t u) {
+    parallel_for_if(large, units.size(), [&](size_t u) {
       const int l = units[u].first, slot = units[u].second / 4, c = units[u].second % 4;
       LevelMaps& M = maps[l];
       ClassMaps& m = per[l][units[u].second];
@@ -1267,12 +1268,13 @@ amr_hierarchy* build_hierarchy(const amr_params* p, const amr_grid* grids, int32
     build_fill_maps(h);
     build_lists(h);
     h->sync.resize(h->nlev);
-    // The levels' entries: on worker threads (level
+    // The levels' entries: of a hierarchy of some size on worker threads (level
     // 1's coarse side is often a single grid: 6.2 ms one level after the other,
     // 4.6 together on 48 grids over 48^3); of a large one level after level, each
-    // uploaded and freed before the next, so that one level's are held at a time.
-    // The device is this thread's, so the uploads stay here.
-    const bool together = h->total_elems <= (1 << 22);
+    // uploaded and freed before the next, so that one level's are held at a time,
+    // and of a small one too.  The device is this thread's, so the uploads stay
+    // here.
+    const bool together = h->total_elems > (1 << 16) && h->total_elems <= (1 << 22);
     std::vector<SyncEntries> sync(h->nlev);
     if (together) {
       parallel_for((size_t)h->nlev - 1, [&](size_t t) {
