@@ -342,7 +342,8 @@ amr_status amr_load_primitive_adjoint(amr_hierarchy* h, int32_t grid, const doub
  * only, the update one block per item (implied for the flux kernel by bit 0);
  * bit 3: one fused flux-update kernel per launch instead of the two (tiles
  * overlapping by two cells, face fluxes kept in LDS; only those the
- * coarse/fine registers read are stored; persistent with bit 0 or 2; the
+ * coarse/fine registers read are stored; persistent with bit 0 or 2 where the
+ * launch has more claims than resident blocks; the
  * upwinded EMF always takes the two-kernel path); bits 4-5: c, each block
  * takes 2^c consecutive work items at a time (grids per workgroup for grids
  * of one tile and one z-chunk; else a run of neighbouring tiles), for every

@@ -546,8 +546,14 @@ void launch_fused(int ndim, const GridDesc* grids, const FluxItem* items, int ni
                   uint32_t parity, DevFlux<T> F, const uint8_t* fmask, const double* dt0, Phys ph, ErrBlock* err,
                   WorkQueue* q, int pblocks, bool xcd, int claim, hipStream_t s) {
   if (nitems <= 0) return;
-  const bool per = pblocks > 0 && q != nullptr;
-  const dim3 grid(per ? std::min(pblocks, nitems) : claim_blocks(nitems, claim, xcd));
+  // A persistent launch pays where its blocks come back for more.  With no more
+  // claims than resident blocks each claim has a block of its own, as without the
+  // queue: the blocks then reach the CUs one by one, while pops leave some CUs two
+  // claims and some none (96^3 in FP64 in claims of two: 293 us from the queue,
+  // 205 so; 258 while a CU held one block).
+  const int claims = claim_blocks(nitems, claim, xcd);
+  const bool per = q != nullptr && pblocks > 0 && claims > pblocks;
+  const dim3 grid(per ? pblocks : claims);
   StatePair<T> SP;
   SP.s[0] = S0;
   SP.s[1] = S1;
