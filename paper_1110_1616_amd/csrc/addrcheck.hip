@@ -4,7 +4,9 @@
 // uniform base pointers (IdxB); the update kernel and the tables by 64-bit
 // element indices (Idx).  For every work list of a hierarchy and an element
 // size of 4, 8 or 16 bytes this walks the work items exactly as the two
-// kernels do (same tile geometry, same per-lane predicates) and checks that
+// kernels and the fused one do (same tile geometry, same per-lane predicates;
+// the fused kernel's loads, which no predicate guards, at their clamped cells)
+// and checks that
 //   - every 32-bit byte offset the flux kernel loads from or stores to is
 //     the 64-bit element offset times the element size (no wrap error);
 //   - every element it touches lies in its grid's padded box;
@@ -12,6 +14,7 @@
 //   - every face flux the update kernel reads (directly, or through the
 //     edge EMFs) was written by the flux kernel of the same launch.
 #include "advance_common.hpp"
+#include "launch_common.hpp"
 #include "runtime_internal.hpp"
 
 using namespace amr;
@@ -205,7 +208,8 @@ template <int NDIM, class T> struct Walker {
     }
   }
 
-  // ---- the fused flux-update kernel (see fused.hip), same predicates ----
+  // ---- the fused flux-update kernel (see fused.hip): the loads of every lane,
+  // and the same predicates for what it forms, updates and stores ----
   // counts of updates per element (cells, B_x, B_y, B_z) and of flux stores
   std::vector<uint8_t>* up;      // [4]
   std::vector<int64_t>* utouch;  // [4]
@@ -255,8 +259,6 @@ template <int NDIM, class T> struct Walker {
       const bool ubx = live && urow && (ucol || (tx >= 1 && cx == uhx));
       const bool uby = live && ucol && (urow || (ty >= 1 && cy == uhy));
       const bool sx = owns(tx, tw, cx, cl, chx - 1), sy = owns(ty, th, cy, cl, chy - 1);
-      const bool rok_dummy = false;
-      (void)rok_dummy;
       // neighbour lanes
       auto nb = [&](int t, bool& nact, bool& nxf, bool& nyf) {
         int a, b;
@@ -269,11 +271,32 @@ template <int NDIM, class T> struct Walker {
       if (ty >= 1) nb(tid - tw, d_act, d_xf, d_yf);
       if (tx + 1 < tw) nb(tid + 1, r_act, r_xf, r_yf);
       if (ty + 1 < th && tid + tw < 256) nb(tid + tw, u_act, u_xf, u_yf);
-      const bool ook = live && cx >= wlo && cx < whix && cy >= wlo && cy < whiy;
-      if (ook) {
-        if (NDIM == 3) load_cell(G, bx, ix, cx, cy, kstart - 1, it);
-        for (int k = kstart; k <= kend + (NDIM == 3 ? 1 : 0); ++k) load_cell(G, bx, ix, cx, cy, k, it);
+      // loads: every lane its cell, clamped into the item's box, of the planes
+      // from the one below the first to the one above the last (their mask bytes
+      // too), and the ring lanes theirs
+      const int lx = std::min(std::max(cx, wlo), whix - 1), ly = std::min(std::max(cy, wlo), whiy - 1);
+      for (int k = NDIM == 3 ? kstart - 1 : 0; k <= (NDIM == 3 ? kend + 1 : 0); ++k) {
+        load_cell(G, bx, ix, lx, ly, k, it);
+        if (mask && (uint64_t)bx(lx, ly, k) / sizeof(T) >= h->h_fmask.size()) bad("fused: mask byte outside", &it, ix(lx, ly, k));
       }
+      const int nring = 2 * (tw + th), kW = tw + 2;
+      bool rok = false;
+      int rx = lx, ry = ly;
+      if (tid < nring) {
+        int rex, rey;
+        ring_entry_host(tid, tw, th, rex, rey);
+        const int rcx = it.x0 - 2 + rex, rcy = it.y0 - 2 + rey;
+        rok = rcx >= wlo && rcx < whix && rcy >= wlo && rcy < whiy;
+        if (rok) {
+          rx = rcx;
+          ry = rcy;
+        }
+        need(rey * kW + rex < kMaxPlane, "ring entry outside the LDS plane", ix(lx, ly, 0));
+      }
+      if (NDIM == 3 || rok)
+        for (int k = NDIM == 3 ? kstart : 0; k <= (NDIM == 3 ? kend : 0); ++k) load_cell(G, bx, ix, rx, ry, k, it);
+      const int eo = live ? (ty + 1) * kW + tx + 1 : kW + 1;
+      need(eo - kW >= 0 && eo + kW < kMaxPlane, "neighbour outside the LDS plane", ix(lx, ly, 0));
       const bool ez = xf && yf;
       if (ez) need(d_xf && l_yf, "E_z reads a face its neighbour lane did not solve", ix(cx, cy, 0));
       for (int k = kstart; k <= kend; ++k) {
