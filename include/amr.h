@@ -433,8 +433,8 @@ int32_t amr_selfcheck_hlld_adjoint(int64_t n, const double* states, const double
 /* Host-only check of the advance kernels' addressing (no GPU needed): builds
  * the hierarchy's tables as amr_validate() does and, for every work list and
  * an element size of elem_bytes (4, 8 or 16), walks the work items as the
- * flux and update kernels do, checking that each 32-bit byte offset the
- * flux kernel loads or stores equals the 64-bit element offset times the
+ * flux, update and fused kernels do, checking that each 32-bit byte offset
+ * the flux and fused kernels load or store equals the 64-bit element offset times the
  * element size, that every access lies in its grid's padded box, that no
  * face flux has two writers in one launch, and that every face flux the
  * update reads (directly or through an edge EMF) was written in the same
@@ -444,6 +444,13 @@ int32_t amr_selfcheck_hlld_adjoint(int64_t n, const double* states, const double
  * 4 GiB. */
 amr_status amr_selfcheck_addressing(const amr_params* p, const amr_grid* grids, int32_t ngrids, int32_t elem_bytes,
                                     int64_t* stats);
+
+/* Host-only: the work lists of the launch cycles of a coarse step, as built for
+ * the default configuration.  cycles <- their number; lists: for each of the
+ * first max_cycles, the flux kernel's items, the planes of its longest item, the
+ * fused kernel's items and the planes of its longest.  Statuses as amr_validate(). */
+amr_status amr_selfcheck_work_lists(const amr_params* p, const amr_grid* grids, int32_t ngrids, int32_t max_cycles,
+                                    int32_t* lists, int32_t* cycles);
 
 /* ---- predictive balancing of launch cycles ----
  * One coarse step runs R^(L-1) launch cycles.  Step k of a level-l grid has

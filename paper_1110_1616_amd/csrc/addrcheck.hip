@@ -474,4 +474,36 @@ amr_status amr_selfcheck_addressing(const amr_params* p, const amr_grid* grids, 
   }
 }
 
+// Items and longest item (planes) of the flux and of the fused list of each
+// launch cycle of a coarse step, as built for the default configuration.
+amr_status amr_selfcheck_work_lists(const amr_params* p, const amr_grid* grids, int32_t ngrids, int32_t max_cycles,
+                                    int32_t* lists, int32_t* cycles) {
+  amr_hierarchy* h = nullptr;
+  try {
+    if (!cycles || (max_cycles > 0 && !lists)) throw Error(AMR_EINVAL, "null argument");
+    g_host_only = true;
+    h = build_hierarchy(p, grids, ngrids);
+    g_host_only = false;
+    *cycles = (int32_t)h->cycle_lists.size();
+    for (int c = 0; c < std::min(*cycles, max_cycles); ++c) {
+      const LaunchList& L = h->cycle_lists[c];
+      auto longest = [](const std::vector<FluxItem>& v, const ListRef& r) {
+        int n = 0;
+        for (int i = 0; i < r.n; ++i) n = std::max(n, v[r.off + i].z1 - v[r.off + i].z0);
+        return n;
+      };
+      lists[4 * c + 0] = L.flux.n;
+      lists[4 * c + 1] = longest(h->h_fitems, L.flux);
+      lists[4 * c + 2] = L.fused.n;
+      lists[4 * c + 3] = longest(h->h_xitems, L.fused);
+    }
+    delete h;
+    return AMR_OK;
+  } catch (const std::exception& e) {
+    g_host_only = false;
+    delete h;
+    return fail(e);
+  }
+}
+
 }  // extern "C"
