@@ -16,7 +16,7 @@
 //                interior elements they were copied from        -> lambda
 // They are bound by their memory traffic (87 arrays) and, the face and cell
 // reverses, by registers (one or two waves a SIMD).  64^3, FP64, a reverse
-// step: 250 us (pred 36, face 84, cell 73, prim 27, assemble 20, fold 10);
+// step: 240 us (pred 36, face 75, cell 73, prim 26, assemble 20, fold 10);
 // it was 338 with the slope choices formed again by k_adj_prim from the
 // states of 27 neighbours (100 us), one thread for a cell's three faces (87),
 // a copy of every own element (10), the fields of k_adj_fold one after the
@@ -205,7 +205,7 @@ __device__ __forceinline__ T edge_lambda(const GridDesc& G, const DevState<T>& L
   return v;
 }
 
-// (a grid row of blocks per direction: three short launches in one, 84 us on
+// (a grid row of blocks per direction: three short launches in one, then 84 us on
 // 64^3 in FP64 against 87 for the three in turn)
 template <class T, int NDIM>
 __global__ __launch_bounds__(256, 2) void k_adj_face(const GridDesc* __restrict__ grids,

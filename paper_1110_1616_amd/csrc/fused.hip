@@ -21,17 +21,18 @@
 // inside single expressions only, so the results equal the two-kernel
 // path's bit for bit.
 //
-// What bounds it: instruction issue.  A plane takes about 1840 vector and
+// What bounds it: instruction issue.  A plane takes about 1860 vector and
 // 450 other instructions a wave in FP64; a wave alone on its SIMD issues at
 // most one of any kind every four cycles and waits for LDS, barriers and
 // dependent FP64 results in between, so two waves share each SIMD: 256
-// registers and 81 KB of LDS a block in FP64, two blocks a CU (159 registers
-// in FP32, three).  To fit, the z differences wait in LDS, W of the next
+// registers (a dozen values in scratch) and 81 KB of LDS a block in FP64, two
+// blocks a CU (157 registers in FP32, three).  To fit, the z differences wait in LDS, W of the next
 // plane is read back from the W plane, and the loads of the next planes are
 // issued behind the Riemann problems instead of a plane ahead.  Against one
 // block a CU with 375 registers, 115 KB and the loads a plane ahead: two
 // steps of a 128^3 grid 770 -> 628 us, two coarse steps of the 549-grid
-// hierarchy 6225 -> 5442 us (FP32: the same within 1%).  Four waves a SIMD
+// hierarchy 6225 -> 5442 us (FP32: the same within 1%); 654 and 5450 us since
+// the fast speeds are divided by the density and both z-fluxes are carried.  Four waves a SIMD
 // in FP32 (128 registers) spill and are 11% slower.  Waves in two roles, one
 // predicting plane k + 1 while another solves plane k, pass every face state
 // through LDS and were 12% slower (14% on the hierarchy).

@@ -308,7 +308,7 @@ __host__ __device__ __forceinline__ void hlld_fan(const T (&ql)[8], const T (&qr
 // not satisfy them: its flux is put right by B_t (u - S_M), under a branch at
 // the end (summed where the states are selected it spilled 30 registers).
 // Against forming every state's jump F + S (U* - U) + S* (U** - U*) with
-// selects between both sides this is about 260 instead of 430 vector
+// selects between both sides this is about 270 instead of 430 vector
 // instructions in double (a select of a double is two), and the kernels here
 // are bound by their issue.
 template <class T>
