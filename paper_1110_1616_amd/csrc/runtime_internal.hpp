@@ -425,8 +425,8 @@ template <class Fn> inline void parallel_for(size_t n, Fn&& fn) {
         thread_share() = share;
         work();
       });
-  } catch (const std::system_error&) {
-    // no more threads to be had: those there are do the work
+  } catch (...) {
+    // no more threads (or memory for one) to be had: those there are do the work
   }
   thread_share() = share;
   work();
